@@ -157,23 +157,28 @@ inline Coef make_coef(double tau, double c2, int model)
     const double om = 1.0 / tau;
     const double w0 = 4.0 / 9.0, w1 = 1.0 / 9.0, w2 = 1.0 / 36.0;
     const double sh = eq_shift(c2, model);
+    const double e1 = sh, e0 = -1.25 * sh;
     Coef k;
-    k.om1 = 1.0 - om;
-    k.wo0 = om * w0;
-    k.wo1 = om * w1;
-    k.wo2 = om * w2;
-    k.as1 = model == LBM_MODEL_EQUILIBRIUM ? 0.0 : source_as1(c2);
-    k.as2 = 0.25 * k.as1;
-    k.e1 = sh;
-    k.e0 = -1.25 * sh;
-    k.om1f = (float)k.om1;
-    k.wo0f = (float)k.wo0;
-    k.wo1f = (float)k.wo1;
-    k.wo2f = (float)k.wo2;
-    k.as1f = (float)k.as1;
-    k.as2f = (float)k.as2;
-    k.e1f = (float)k.e1;
-    k.e0f = (float)k.e0;
+    k.d.om1 = 1.0 - om;
+    k.d.a0 = om * w0 * (1.0 + e0);
+    k.d.a1 = om * w1 * (1.0 + e1);
+    k.d.a2 = om * w2 * (1.0 + e1);
+    k.d.b0 = -1.5 * om * w0;
+    k.d.b1 = -1.5 * om * w1;
+    k.d.b2 = 3.0 * om * w2;
+    k.d.z0 = om * w0 * e0;
+    k.d.z1 = om * w1 * e1;
+    k.d.z2 = om * w2 * e1;
+    k.d.t45 = 4.5 * om * w1;
+    k.d.t9 = 9.0 * om * w2;
+    k.d.w3 = 3.0 * om * w1;
+    k.d.as1 = model == LBM_MODEL_EQUILIBRIUM ? 0.0 : source_as1(c2);
+    k.d.e1 = e1;
+    k.d.e0 = e0;
+    const CoefSet<double>& d = k.d;
+    k.f = CoefSet<float>{(float)d.om1, (float)d.a0, (float)d.a1, (float)d.a2, (float)d.b0,  (float)d.b1,
+                         (float)d.b2,  (float)d.z0, (float)d.z1, (float)d.z2, (float)d.t45, (float)d.t9,
+                         (float)d.w3,  (float)d.as1, (float)d.e1, (float)d.e0};
     return k;
 }
 

@@ -32,20 +32,26 @@ struct Geom {
 };
 
 // Collision / source coefficients of Eq. 5 in the delta form used by the
-// kernels (d_i = f_i - w_i):
-//   d*_0 = om1 d_0 + wo0 A
-//   d*_i = om1 d_i + P + Q,  d*_opp = om1 d_opp + P - Q        (pairs)
-// with om = 1/tau, om1 = 1 - om, wo_k = om w_k, and as_k = 3 w_k alpha / 2:
-// the source term 3 w_k alpha (e_i . grad rho) is applied to the undivided
-// central differences rho(x + 1) - rho(x - 1), so the 1/2 of the central
-// difference sits in the coefficient (an exact power-of-two scaling).
+// kernels (d_i = f_i - w_i; see collide_col in step.h), with om = 1/tau and
+// the index 0, 1, 2 for the rest, axis and diagonal links:
+//   om1 = 1 - om;
+//   a_k = om w_k (1 + e_k) multiplies drho in the even part, b_k (-3/2 om w_0,
+//   -3/2 om w_1, 3 om w_2) multiplies j.u, and z_k = om w_k e_k is its
+//   constant (FP64 arithmetic, centred on the weights);
+//   t45 = 9/2 om w_1, t9 = 9 om w_2, w3 = 3 om w_1;
+//   as1 = 3 w_1 alpha / 2: the source term 3 w_1 alpha (e_i . grad rho) is
+//   applied to the undivided central differences rho(x + 1) - rho(x - 1), so
+//   the 1/2 of the central difference sits in the coefficient (an exact
+//   power-of-two scaling).
 // e1, e0 shift the equilibrium for the altered-equilibrium model (0 for the
-// paper's model): the moving pairs relax towards A + rho e1 in place of A,
-// the rest population towards A + rho e0. The FP32-compute kernels take the
-// same values rounded once to FP32.
+// paper's model): e1 for the moving links (e_1 = e_2), e0 for the rest one.
+template <class C> struct CoefSet {
+    C om1, a0, a1, a2, b0, b1, b2, z0, z1, z2, t45, t9, w3, as1, e1, e0;
+};
+// In FP64, and the same values rounded once to FP32.
 struct Coef {
-    double om1, wo0, wo1, wo2, as1, as2, e1, e0;
-    float om1f, wo0f, wo1f, wo2f, as1f, as2f, e1f, e0f;
+    CoefSet<double> d;
+    CoefSet<float> f;
 };
 
 // One lattice as seen by a step launch.
@@ -60,8 +66,8 @@ struct StepTile {
     int rowband;  // tile order: 1 = strip groups of a chunk first
     int xcd_chunk;  // vertical-stack tile order over the 8 XCDs (see xcd_tile in step.h)
     // Per-site source coefficients (a c2 field): field[y * fpitch + x] =
-    // as1 at site (x, y) in compute precision (as2 = as1 / 4); nullptr for
-    // the uniform coefficients of c.
+    // as1 at site (x, y) in compute precision; nullptr for the uniform one
+    // of c.
     const void* field;
     int fpitch;
 };
@@ -71,7 +77,7 @@ struct StepTile {
 inline bool grid_fits(long long blocks, int threads) { return blocks * threads <= 0xffffffffLL; }
 
 // The source coefficient of the axis links, as1 = 3 w_1 alpha / 2 with
-// alpha = 1/3 - c2 (Eq. 8; the diagonal links take as2 = as1 / 4, exactly,
+// alpha = 1/3 - c2 (Eq. 8; the diagonal links take a quarter of it, exactly,
 // since w_2 = w_1 / 4). One definition for the uniform coefficients and the
 // per-site field, so that a uniform field gives the same bits.
 __host__ __device__ inline double source_as1(double c2)
