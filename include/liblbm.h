@@ -215,6 +215,9 @@ size_t lbm_footprint_bytes(int nx, int ny, int dtype);
  * step while inlet/outlet boundaries are set, use the single-step vertical
  * stack (vx = 2, nw = 8, non-temporal stores). The
  * results are those of single steps, bit for bit (c2 fields included).
+ * With the dtype's default shape, lattices large enough (from about 700^2
+ * sites) that fit the row-interleaved layout advance four steps per launch
+ * instead (the cascade kernel); the pairs take what is left of a count.
  * lbm_get_tile: any pointer may be NULL. */
 enum lbm_tile_flags {
     LBM_TILE_PREFETCH = 1, /* issue the next row's loads before relaxing the current row */
@@ -228,7 +231,8 @@ int lbm_set_tile(lbm_lattice* L, int vx, int nw, int h, int flags);
 int lbm_get_tile(const lbm_lattice* L, int* vx, int* nw, int* h, int* flags);
 
 /* Autotuner: time the candidate kernel shapes on this lattice, single- and
- * two-step, each over two steps (reps timed rounds each, after warm-up
+ * two-step and the default shape's four-step passes, each over four steps
+ * (reps timed rounds each, after warm-up
  * launches; every launch reads the current state and writes the spare
  * buffer, so the state is unchanged) and apply the fastest. With use_cache != 0 a shape found before for the same GPU
  * architecture, dtype and nx x ny is applied without timing. Results are

@@ -38,6 +38,11 @@ hipError_t launch_batch2_persistent(int dtype, int vx, int nw, bool nts, const B
 // takes one step, one with nsteps <= 2p none.
 hipError_t launch_batch2(int dtype, int vx, int nw, bool nts, const BatchLat* lats, const int* item_lat, int nitems,
                          int p, int ch, hipStream_t st);
+// kCascadeSteps steps per launch (cascade.hip); t's strips and chunks of t.h
+// rows are those of cascade_cols. The caller brings the ghost columns up to
+// date (launch_ghosts) after the last launch of a call.
+hipError_t launch_cascade(int dtype, int vx, const StepTile& t, hipStream_t st);
+hipError_t launch_ghosts(int dtype, void* s, const Geom& g, hipStream_t st);
 hipError_t launch_init(int dtype, void* s, const Geom& g, const double* rho, const double* ux, const double* uy,
                        double eqs, hipStream_t st);
 hipError_t launch_xbc(int dtype, void* s, const Geom& g, double rho_in, double eqs, hipStream_t st);

@@ -8,6 +8,7 @@
 #include <cstring>
 #include <new>
 
+#include "cascade.h"
 #include "host.h"
 #include "tune.h"
 
@@ -30,6 +31,7 @@ struct lbm_lattice {
     bool ready;
     int vx, nw, h;     // step tile
     int kflags;        // LBM_TILE_* bits
+    CascadeShape deep; // four-step passes of the default shape (see cascade_of)
     void* field;       // per-site source coefficients of a c2 field, or nullptr
     int fpitch;        // its row pitch (elements)
     int xbc;           // lbm_xbc
@@ -127,6 +129,27 @@ StepTile make_tile(const lbm_lattice* L)
     return t;
 }
 
+// The four-step passes of a lattice (vx = 0: none): those of the default
+// shape, where they are faster than its two-step ones, and where a buffer is
+// within reach of 32-bit offsets (the row-interleaved layout).
+CascadeShape cascade_of(const lbm_lattice* L)
+{
+    const TileDefault td = default_tile(L->dtype);
+    if (L->vx != td.vx || L->nw != td.nw || L->kflags != td.flags || L->g.rs != 9LL * L->g.pitch) return {};
+    return L->deep;
+}
+
+StepTile cascade_tile(const lbm_lattice* L, const CascadeShape& c)
+{
+    StepTile t = make_tile(L);
+    const int w = cascade_cols(c.vx, kCascadeSteps, L->esize);
+    t.h = c.h;
+    t.nstrips = (L->nx + w - 1) / w;
+    t.nchunks = (L->ny + c.h - 1) / c.h;
+    t.xcd_chunk = 0;  // one run of chunks per XCD: neighbouring strips share their halo's lines in its L2
+    return t;
+}
+
 // A lattice with a c2 field steps with the vertical-stack kernels (single-
 // or two-step) only: a march-form tile is replaced by the dtype's default.
 void field_tile(lbm_lattice* L)
@@ -214,6 +237,7 @@ lbm_lattice* lbm_create(int nx, int ny, double tau, double c2, int dtype)
     L->h = td.h;
     L->kflags = td.flags;
     apply_tile_env(dtype, &L->vx, &L->nw, &L->h, &L->kflags);
+    L->deep = lbm::cascade_shape(dtype, nx, ny);
     hipError_t e = hipGetDevice(&L->device);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&L->own, hipStreamNonBlocking);
     if (e != hipSuccess) {
@@ -305,19 +329,23 @@ int lbm_autotune(lbm_lattice* L, int reps, int use_cache)
         cands.erase(std::remove_if(cands.begin(), cands.end(),
                                    [](const TileCand& k) { return !(k.flags & LBM_TILE_VSTACK); }),
                     cands.end());
-    // Each candidate is timed over two steps (two single-step launches or
-    // one two-step launch), reading cur and writing nxt with no swap: the
-    // state does not change.
+    // Each candidate is timed over four steps, as lbm_step would launch them
+    // (the inlet's steps aside), reading cur and writing nxt with no swap:
+    // the state does not change.
     auto launch = [&](const TileCand& k) -> hipError_t {
         lbm_lattice tmp = *L;
         tmp.vx = k.vx;
         tmp.nw = k.nw;
         tmp.h = k.h;
         tmp.kflags = k.flags;
+        const CascadeShape deep = cascade_of(&tmp);
+        if (deep.vx) return launch_cascade(L->dtype, deep.vx, cascade_tile(&tmp, deep), L->stream);
         const StepTile t = make_tile(&tmp);
-        if (k.flags & LBM_TILE_TWO_STEP) return launch_step2(L->dtype, k.vx, k.nw, k.flags, t, L->stream);
-        hipError_t e = launch_step(L->dtype, k.vx, k.nw, k.flags, t, L->stream);
-        if (e == hipSuccess) e = launch_step(L->dtype, k.vx, k.nw, k.flags, t, L->stream);
+        const bool pairs = (k.flags & LBM_TILE_TWO_STEP) != 0;
+        hipError_t e = hipSuccess;
+        for (int r = 0; r < (pairs ? 2 : 4) && e == hipSuccess; ++r)
+            e = pairs ? launch_step2(L->dtype, k.vx, k.nw, k.flags, t, L->stream)
+                      : launch_step(L->dtype, k.vx, k.nw, k.flags, t, L->stream);
         return e;
     };
     float us = 0;
@@ -436,10 +464,12 @@ int lbm_step(lbm_lattice* L, int n)
 {
     if (!L || n < 0) return LBM_EINVAL;
     if (!L->ready) return LBM_ESTATE;
-    // A two-step shape advances two steps per launch; a lone last step, and
-    // every step of a lattice with inlet/outlet boundaries (applied after
-    // each step), take the dtype's default single-step shape.
+    // The default shape advances four steps per launch where that is faster
+    // (see cascade_of), a two-step shape two; a lone last step, and every
+    // step of a lattice with inlet/outlet boundaries (applied after each
+    // step), take the dtype's default single-step shape.
     const bool two = (L->kflags & LBM_TILE_TWO_STEP) != 0;
+    const CascadeShape deep = L->xbc == LBM_XBC_INLET_OUTLET ? CascadeShape{} : cascade_of(L);
     lbm_lattice one = *L;
     if (two) {
         const TileDefault td = default_single_tile(L->dtype);
@@ -451,7 +481,11 @@ int lbm_step(lbm_lattice* L, int n)
     for (int k = 0; k < n;) {
         hipError_t e;
         int done = 1;
-        if (two && L->xbc != LBM_XBC_INLET_OUTLET && n - k >= 2) {
+        if (deep.vx && n - k >= kCascadeSteps) {
+            e = launch_cascade(L->dtype, deep.vx, cascade_tile(L, deep), L->stream);
+            done = kCascadeSteps;
+            if (n - k - done < kCascadeSteps && e == hipSuccess) e = launch_ghosts(L->dtype, L->nxt, L->g, L->stream);
+        } else if (two && L->xbc != LBM_XBC_INLET_OUTLET && n - k >= 2) {
             e = launch_step2(L->dtype, L->vx, L->nw, L->kflags, make_tile(L), L->stream);
             done = 2;
         } else {
