@@ -54,8 +54,11 @@ hipError_t launch_get_f(int dtype, const void* s, const Geom& g, double* f, doub
 int moments_blocks(const Geom& g);
 hipError_t launch_sample_f(int dtype, const void* s, const Geom& g, int n, const int* xy, double* out, double eqs,
                            hipStream_t st);
+// Fields (any may be nullptr) and totals (device-visible memory) in one
+// launch; partials: 3 moments_blocks(g) doubles, done: the buffer's counter
+// word (done_word), zero between launches.
 hipError_t launch_moments(int dtype, const void* s, const Geom& g, double* rho, double* ux, double* uy,
-                          double* partials, double* totals, hipStream_t st);
+                          double* partials, unsigned* done, double* totals, hipStream_t st);
 // Words of barrier and work-counter state a persistent batched launch
 // needs (device memory the pool allocates once; see the persistent kernel).
 constexpr int kPoolBarWords = 24;
@@ -143,6 +146,12 @@ inline size_t footprint(const Geom& g, int esize)
 {
     // 2 buffers, plus one line of slack past the end.
     return (size_t)2 * (size_t)buffer_elems(g) * esize + kLineBytes;
+}
+// The first word of that line counts finished workgroups (launch_moments);
+// zeroed with the buffers.
+inline unsigned* done_word(void* buf, const Geom& g, int esize)
+{
+    return (unsigned*)((char*)buf + (size_t)2 * (size_t)buffer_elems(g) * esize);
 }
 
 inline size_t red_doubles(const Geom& g) { return (size_t)3 * moments_blocks(g) + 3; }

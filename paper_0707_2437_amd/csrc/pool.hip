@@ -108,6 +108,7 @@ struct lbm_pool {
     BatchLat* d_lats = nullptr;   // device descriptor array
     int* d_items = nullptr;       // device item -> lattice map
     unsigned* d_bar = nullptr;    // barrier state of the persistent kernel (kPoolBarWords words)
+    double* tot = nullptr;        // totals of lbm_pool_moments, in pinned host memory the device writes
     int cap = 0, item_cap = 0;
     int per_item = 1;             // tiles per work item
     int xcd_chunk = 8;            // items per XCD chunk of the grouped launches (see xcd_tile)
@@ -328,11 +329,13 @@ lbm_pool* lbm_pool_create(size_t budget_bytes, int dtype)
     if (e == hipSuccess) e = noalloc_scratch(P->device, &noalloc_base);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&P->own, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipMalloc((void**)&P->d_bar, kPoolBarWords * sizeof(unsigned));
+    if (e == hipSuccess) e = hipHostMalloc((void**)&P->tot, 3 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent);
     if (e == hipSuccess) e = hipMemsetAsync(P->d_bar, 0, kPoolBarWords * sizeof(unsigned), P->own);
     if (e == hipSuccess) e = hipStreamSynchronize(P->own);
     if (e != hipSuccess) {
         g_pool_error = LBM_EDEVICE;
         if (P->d_bar) (void)hipFree(P->d_bar);
+        if (P->tot) (void)hipHostFree(P->tot);
         if (P->own) (void)hipStreamDestroy(P->own);
         delete P;
         return nullptr;
@@ -351,6 +354,7 @@ void lbm_pool_destroy(lbm_pool* P)
     if (P->d_lats) (void)hipFree(P->d_lats);
     if (P->d_items) (void)hipFree(P->d_items);
     if (P->d_bar) (void)hipFree(P->d_bar);
+    if (P->tot) (void)hipHostFree(P->tot);
     if (P->own) (void)hipStreamDestroy(P->own);
     delete P;
 }
@@ -570,16 +574,15 @@ int lbm_pool_moments(lbm_pool* P, int slot, double* rho, double* ux, double* uy,
     DevScratch d;
     hipError_t e = (rho || ux || uy) ? d.alloc(3 * n, P->stream) : hipSuccess;
     double* dp[3] = {rho ? d.p : nullptr, ux ? d.p + n : nullptr, uy ? d.p + 2 * n : nullptr};
-    double* tot_dev = S->red + (size_t)3 * moments_blocks(S->g);
-    double tot[3] = {0, 0, 0};
     if (e == hipSuccess)
-        e = launch_moments(P->dtype, cur_buf(*S), S->g, dp[0], dp[1], dp[2], S->red, tot_dev, P->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(tot, tot_dev, sizeof(tot), hipMemcpyDeviceToHost, P->stream);
+        e = launch_moments(P->dtype, cur_buf(*S), S->g, dp[0], dp[1], dp[2], S->red,
+                           done_word(S->buf, S->g, P->esize), P->tot, P->stream);
     double* host[3] = {rho, ux, uy};
     for (int c = 0; c < 3 && e == hipSuccess; ++c)
         if (host[c]) e = hipMemcpyAsync(host[c], dp[c], n * sizeof(double), hipMemcpyDeviceToHost, P->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(P->stream);
     if (e != hipSuccess) return status_of(e);
+    const double tot[3] = {P->tot[0], P->tot[1], P->tot[2]};
     if (totals) std::memcpy(totals, tot, sizeof(tot));
     const int be = take_barrier_error(P);
     if (be != LBM_OK) return be;
@@ -593,7 +596,8 @@ int lbm_pool_totals_device(lbm_pool* P, int slot, double* totals)
     Slot* S = slot_of(P, slot);
     if (!S || !totals) return LBM_EINVAL;
     if (!S->ready) return LBM_ESTATE;
-    return status_of(launch_moments(P->dtype, cur_buf(*S), S->g, nullptr, nullptr, nullptr, S->red, totals, P->stream));
+    return status_of(launch_moments(P->dtype, cur_buf(*S), S->g, nullptr, nullptr, nullptr, S->red,
+                                    done_word(S->buf, S->g, P->esize), totals, P->stream));
 }
 
 int lbm_pool_get_f(lbm_pool* P, int slot, double* f)
