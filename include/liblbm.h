@@ -112,7 +112,8 @@ int lbm_set_model(lbm_lattice* L, int model);
  * cut: a population that would cross it arrives as the equilibrium
  * population of the column it enters, at that column's boundary density.
  * t is lbm_time() (so lbm_init / lbm_set_f restart the inlet's phase). Each
- * step then adds one small launch (the two columns). LBM_EINVAL for a NULL
+ * step then adds one small launch (the two columns), except on lattices
+ * small enough for the block kernel (see lbm_set_tile). LBM_EINVAL for a NULL
  * handle, an unknown mode, or the inlet/outlet with nx < 5, a period that
  * is not finite and > 0, or |amplitude| >= 1. Takes effect at the next
  * step; pools are periodic. */
@@ -218,6 +219,9 @@ size_t lbm_footprint_bytes(int nx, int ny, int dtype);
  * With the dtype's default shape, lattices large enough (from about 700^2
  * sites) that fit the row-interleaved layout advance four steps per launch
  * instead (the cascade kernel); the pairs take what is left of a count.
+ * Small lattices (at most 16 rows, or up to about 250^2 sites) advance up to
+ * 15 or 4 steps per launch (the block kernel), inlet/outlet boundaries
+ * included.
  * lbm_get_tile: any pointer may be NULL. */
 enum lbm_tile_flags {
     LBM_TILE_PREFETCH = 1, /* issue the next row's loads before relaxing the current row */

@@ -8,6 +8,7 @@
 #include <cstdlib>
 #include <cstring>
 
+#include "block.h"
 #include "internal.h"
 #include "liblbm.h"
 #include "step2.h"
@@ -42,6 +43,8 @@ hipError_t launch_batch2(int dtype, int vx, int nw, bool nts, const BatchLat* la
 // rows are those of cascade_cols. The caller brings the ghost columns up to
 // date (launch_ghosts) after the last launch of a call.
 hipError_t launch_cascade(int dtype, int vx, const StepTile& t, hipStream_t st);
+// b.ns steps per launch on small lattices (block.hip).
+hipError_t launch_block(int dtype, const BlockShape& b, const StepTile& t, const BlockInlet* inlet, hipStream_t st);
 hipError_t launch_ghosts(int dtype, void* s, const Geom& g, hipStream_t st);
 hipError_t launch_init(int dtype, void* s, const Geom& g, const double* rho, const double* ux, const double* uy,
                        double eqs, hipStream_t st);

@@ -32,7 +32,7 @@ struct lbm_lattice {
     bool ready;
     int vx, nw, h;     // step tile
     int kflags;        // LBM_TILE_* bits
-    CascadeShape deep; // four-step passes of the default shape (see cascade_of)
+    CascadeShape deep; // cascade passes of the default shape (see next_pass)
     void* field;       // per-site source coefficients of a c2 field, or nullptr
     int fpitch;        // its row pitch (elements)
     int xbc;           // lbm_xbc
@@ -130,25 +130,73 @@ StepTile make_tile(const lbm_lattice* L)
     return t;
 }
 
-// The four-step passes of a lattice (vx = 0: none): those of the default
-// shape, where they are faster than its two-step ones, and where a buffer is
-// within reach of 32-bit offsets (the row-interleaved layout).
-CascadeShape cascade_of(const lbm_lattice* L)
+// The next launch of a lattice with n steps to take: the steps it takes and
+// the kernel. The default shape takes, where they are faster, block passes
+// (small lattices) or cascade passes (large ones, whose buffer is within
+// reach of 32-bit offsets: the row-interleaved layout); a two-step shape
+// takes pairs; a lone last step, and the steps of a lattice with inlet/outlet
+// boundaries that no block pass takes (launch_xbc follows each), the dtype's
+// default single-step shape; any other shape itself.
+struct Pass {
+    enum Kind { kStep, kPair, kCascade, kBlock } kind;
+    int steps;
+    BlockShape block;
+};
+Pass next_pass(const lbm_lattice* L, int n)
 {
+    const bool inlet = L->xbc == LBM_XBC_INLET_OUTLET;
     const TileDefault td = default_tile(L->dtype);
-    if (L->vx != td.vx || L->nw != td.nw || L->kflags != td.flags || L->g.rs != 9LL * L->g.pitch) return {};
-    return L->deep;
+    if (L->vx == td.vx && L->nw == td.nw && L->kflags == td.flags) {
+        if (!(inlet && L->field)) {
+            const BlockShape b = block_shape(L->dtype, L->nx, L->ny, n, inlet);
+            if (b.ns) return {Pass::kBlock, b.ns, b};
+        }
+        if (!inlet && L->deep.vx && n >= kCascadeSteps && L->g.rs == 9LL * L->g.pitch)
+            return {Pass::kCascade, kCascadeSteps, {}};
+    }
+    if ((L->kflags & LBM_TILE_TWO_STEP) && !inlet && n >= 2) return {Pass::kPair, 2, {}};
+    return {Pass::kStep, 1, {}};
 }
 
-StepTile cascade_tile(const lbm_lattice* L, const CascadeShape& c)
+// Launch pass p of the lattice's state at time L->t, from cur to nxt. last:
+// the pass after it is not a cascade.
+hipError_t launch_pass(const lbm_lattice* L, const Pass& p, bool last)
 {
     StepTile t = make_tile(L);
-    const int w = cascade_cols(c.vx, kCascadeSteps, L->esize);
-    t.h = c.h;
-    t.nstrips = (L->nx + w - 1) / w;
-    t.nchunks = (L->ny + c.h - 1) / c.h;
-    t.xcd_chunk = 0;  // one run of chunks per XCD: neighbouring strips share their halo's lines in its L2
-    return t;
+    switch (p.kind) {
+    case Pass::kBlock: {
+        t.nstrips = (L->nx + p.block.cols() - 1) / p.block.cols();
+        t.nchunks = (L->ny + p.block.rows(L->ny) - 1) / p.block.rows(L->ny);
+        const BlockInlet in{L->amp, L->period, L->t, eq_shift(L->c2, L->model)};
+        return launch_block(L->dtype, p.block, t, L->xbc == LBM_XBC_INLET_OUTLET ? &in : nullptr, L->stream);
+    }
+    case Pass::kCascade: {
+        const int w = cascade_cols(L->deep.vx, kCascadeSteps, L->esize);
+        t.h = L->deep.h;
+        t.nstrips = (L->nx + w - 1) / w;
+        t.nchunks = (L->ny + t.h - 1) / t.h;
+        t.xcd_chunk = 0;  // one run of chunks per XCD: neighbouring strips share their halo's lines in its L2
+        hipError_t e = launch_cascade(L->dtype, L->deep.vx, t, L->stream);
+        if (e == hipSuccess && last) e = launch_ghosts(L->dtype, L->nxt, L->g, L->stream);
+        return e;
+    }
+    case Pass::kPair: return launch_step2(L->dtype, L->vx, L->nw, L->kflags, t, L->stream);
+    default: break;
+    }
+    lbm_lattice one = *L;
+    if (L->kflags & LBM_TILE_TWO_STEP) {
+        const TileDefault td = default_single_tile(L->dtype);
+        one.vx = td.vx;
+        one.nw = td.nw;
+        one.h = td.h;
+        one.kflags = td.flags;
+        t = make_tile(&one);
+    }
+    hipError_t e = launch_step(L->dtype, one.vx, one.nw, one.kflags, t, L->stream);
+    if (e == hipSuccess && L->xbc == LBM_XBC_INLET_OUTLET)
+        e = launch_xbc(L->dtype, L->nxt, L->g, inlet_density(L->amp, L->period, L->t), eq_shift(L->c2, L->model),
+                       L->stream);
+    return e;
 }
 
 // A lattice with a c2 field steps with the vertical-stack kernels (single-
@@ -333,22 +381,21 @@ int lbm_autotune(lbm_lattice* L, int reps, int use_cache)
                                    [](const TileCand& k) { return !(k.flags & LBM_TILE_VSTACK); }),
                     cands.end());
     // Each candidate is timed over four steps, as lbm_step would launch them
-    // (the inlet's steps aside), reading cur and writing nxt with no swap:
-    // the state does not change.
+    // (the inlet aside), reading cur and writing nxt with no swap: the state
+    // does not change.
     auto launch = [&](const TileCand& k) -> hipError_t {
         lbm_lattice tmp = *L;
         tmp.vx = k.vx;
         tmp.nw = k.nw;
         tmp.h = k.h;
         tmp.kflags = k.flags;
-        const CascadeShape deep = cascade_of(&tmp);
-        if (deep.vx) return launch_cascade(L->dtype, deep.vx, cascade_tile(&tmp, deep), L->stream);
-        const StepTile t = make_tile(&tmp);
-        const bool pairs = (k.flags & LBM_TILE_TWO_STEP) != 0;
+        tmp.xbc = LBM_XBC_PERIODIC;
         hipError_t e = hipSuccess;
-        for (int r = 0; r < (pairs ? 2 : 4) && e == hipSuccess; ++r)
-            e = pairs ? launch_step2(L->dtype, k.vx, k.nw, k.flags, t, L->stream)
-                      : launch_step(L->dtype, k.vx, k.nw, k.flags, t, L->stream);
+        for (int n = 4; n > 0 && e == hipSuccess;) {
+            const Pass p = next_pass(&tmp, n);
+            e = launch_pass(&tmp, p, true);
+            n -= p.steps;
+        }
         return e;
     };
     float us = 0;
@@ -467,44 +514,15 @@ int lbm_step(lbm_lattice* L, int n)
 {
     if (!L || n < 0) return LBM_EINVAL;
     if (!L->ready) return LBM_ESTATE;
-    // The default shape advances four steps per launch where that is faster
-    // (see cascade_of), a two-step shape two; a lone last step, and every
-    // step of a lattice with inlet/outlet boundaries (applied after each
-    // step), take the dtype's default single-step shape.
-    const bool two = (L->kflags & LBM_TILE_TWO_STEP) != 0;
-    const CascadeShape deep = L->xbc == LBM_XBC_INLET_OUTLET ? CascadeShape{} : cascade_of(L);
-    lbm_lattice one = *L;
-    if (two) {
-        const TileDefault td = default_single_tile(L->dtype);
-        one.vx = td.vx;
-        one.nw = td.nw;
-        one.h = td.h;
-        one.kflags = td.flags;
-    }
     for (int k = 0; k < n;) {
-        hipError_t e;
-        int done = 1;
-        if (deep.vx && n - k >= kCascadeSteps) {
-            e = launch_cascade(L->dtype, deep.vx, cascade_tile(L, deep), L->stream);
-            done = kCascadeSteps;
-            if (n - k - done < kCascadeSteps && e == hipSuccess) e = launch_ghosts(L->dtype, L->nxt, L->g, L->stream);
-        } else if (two && L->xbc != LBM_XBC_INLET_OUTLET && n - k >= 2) {
-            e = launch_step2(L->dtype, L->vx, L->nw, L->kflags, make_tile(L), L->stream);
-            done = 2;
-        } else {
-            one.cur = L->cur;
-            one.nxt = L->nxt;
-            e = launch_step(L->dtype, one.vx, one.nw, one.kflags, make_tile(&one), L->stream);
-            if (e == hipSuccess && L->xbc == LBM_XBC_INLET_OUTLET)
-                e = launch_xbc(L->dtype, L->nxt, L->g, inlet_density(L->amp, L->period, L->t),
-                               eq_shift(L->c2, L->model), L->stream);
-        }
+        const Pass p = next_pass(L, n - k);
+        k += p.steps;
+        const hipError_t e = launch_pass(L, p, k == n || next_pass(L, n - k).kind != Pass::kCascade);
         if (e != hipSuccess) return status_of(e);
         void* tmp = L->cur;
         L->cur = L->nxt;
         L->nxt = tmp;
-        L->t += done;
-        k += done;
+        L->t += p.steps;
     }
     return LBM_OK;
 }
