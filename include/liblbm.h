@@ -360,6 +360,9 @@ int lbm_pool_set_mode(lbm_pool* P, int mode, int max_grid);
  * between grid barriers) takes two steps of every listed lattice (the
  * shapes of lbm_set_tile's two-step form); a lattice with an odd step count
  * takes its last step alone in the last one. LBM_EINVAL for other shapes.
+ * With the default two-step tile, grouped and graph calls advance batches of
+ * more than about 0.3 M sites by four steps per launch (cascade passes), the
+ * slots' remainders of four in two-step launches before them.
  * Does not change results (bitwise). lbm_pool_get_tile reports
  * LBM_TILE_TWO_STEP and LBM_TILE_NT_STORE. */
 int lbm_pool_set_tile(lbm_pool* P, int vx, int nw, int flags);
@@ -370,7 +373,7 @@ int lbm_pool_get_tile(const lbm_pool* P, int* vx, int* nw, int* flags);
 int lbm_pool_set_items(lbm_pool* P, int tiles_per_item);
 /* Autotuner for the batched kernels (see lbm_autotune): shape, stores,
  * tiles per item and the order in which items are dealt to the GPU's
- * chiplets, single- and two-step tiles, each timed over two steps of the
+ * chiplets, single- and two-step tiles, each timed over four steps of the
  * listed slots without advancing them (in LBM_POOL_PERSISTENT mode, on
  * persistent launches, whose best shape differs); cached per
  * architecture, mode, dtype, and the batch's

@@ -36,5 +36,7 @@ struct CascadeShape {
     int vx = 0, h = 0;
 };
 CascadeShape cascade_shape(int dtype, int nx, int ny);
+// The shape of a batch of lattices of the given sizes (nx[k] x ny[k]).
+CascadeShape cascade_batch_shape(int dtype, const int* nx, const int* ny, int count);
 
 }  // namespace lbm

@@ -445,13 +445,50 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MW, MW))) vo
         cascade_tile<T, SHIFT, VX, NS, FIELD, RC, false>(a, a.src, a.dst, strip, chunk);
 }
 
+// Batched form: pass p of every lattice of a batch (BatchLat in internal.h,
+// with nsteps counting cascade passes and t0 the buffer time at the first);
+// one wave per item, an item being one strip of one chunk, dealt to the XCDs
+// four at a time (neighbouring strips share their halo's lines in an L2; one
+// run per XCD and single items measured within 2 % of it).
+template <class T, bool SHIFT, int VX, int NS, int MW>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MW, MW))) void batch_cascade_kernel(
+    const BatchLat* __restrict__ lats, const int* __restrict__ item_lat, int nitems, int p)
+{
+    constexpr bool RC = ModelCentred<typename CompT<T>::type>::value;
+    constexpr int es = sizeof(T), W = cascade_cols(VX, NS, es), HL = cascade_halo_lanes(VX, NS, es);
+    const int i = xcd_tile(blockIdx.x, gridDim.x, 4);
+    if (i >= nitems) return;
+    const BatchLat& L = lats[item_lat[i]];
+    if (p >= L.nsteps) return;
+    const bool odd = ((L.t0 + p) & 1) != 0;
+    const void* src = odd ? L.tile.dst : L.tile.src;
+    void* dst = odd ? const_cast<void*>(L.tile.src) : L.tile.dst;
+    const int t = i - L.item_begin;
+    const int strip = t % L.tile.nstrips, chunk = t / L.tile.nstrips;
+    const int x0 = strip * W - HL * VX;
+    if (x0 - 1 < 0 || x0 + 64 * VX + 1 > L.tile.g.nx)
+        cascade_tile<T, SHIFT, VX, NS, false, RC, true>(L.tile, src, dst, strip, chunk);
+    else
+        cascade_tile<T, SHIFT, VX, NS, false, RC, false>(L.tile, src, dst, strip, chunk);
+}
+
+// The time a row takes on MI355X, in us: `alone` for a wave that has its
+// SIMD to itself (the latency of the four levels' chain), `shared` per wave
+// where several share one (instruction issue); waves: per SIMD that the
+// registers allow.
+struct CascadeCost {
+    int dtype, vx, waves;
+    double alone, shared;
+};
+static const CascadeCost kCosts[] = {{0, 1, 2, 1.25, 1.10}, {1, 1, 3, 0.85, 0.62}, {1, 2, 2, 1.45, 1.20},
+                                     {2, 1, 3, 0.72, 0.55}, {2, 2, 2, 1.25, 1.05}, {3, 2, 3, 1.70, 1.25}};
+constexpr int kSimds = 1024;
+
 // Which shape, if any. A chunk of h rows takes h + 14 rows of work, so
 // few tall chunks waste least, but the GPU needs a wave on each of its 1024
 // SIMDs, and the last wave of an uneven count runs alone. The estimate counts
-// both with the time a row takes on MI355X: `alone` for a wave that has its
-// SIMD to itself (the latency of the four levels' chain), `shared` per wave
-// where several share one (instruction issue), in us, from fits over 14
-// lattice sizes of 64^2 to 4099 x 2731 (within 10 % there); with a floor for
+// both with the times of CascadeCost, from fits over 14 lattice sizes of 64^2
+// to 4099 x 2731 (within 10 % there), with a floor for
 // the memory traffic. The two-step kernel takes t0 + t1 per million sites
 // and step. Measured at the crossing (FP32, us per step, two-step against
 // cascade): 512^2 4.5 and 4.9, 700^2 6.5 and 6.1, 1000 x 777 8.9 and 7.1,
@@ -459,14 +496,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MW, MW))) vo
 // 2048^2 21.6 and 23.5, 4099 x 2731 69.9 and 42.9.
 CascadeShape cascade_shape(int dtype, int nx, int ny)
 {
-    struct Cost {
-        int dtype, vx, waves;  // waves: per SIMD that the registers allow
-        double alone, shared;
-    };
-    static const Cost costs[] = {{0, 1, 2, 1.25, 1.10}, {1, 1, 3, 0.85, 0.62}, {1, 2, 2, 1.45, 1.20},
-                                 {2, 1, 3, 0.72, 0.55}, {2, 2, 2, 1.25, 1.05}, {3, 2, 3, 1.70, 1.25}};
     static const double two_step[4][2] = {{2.4, 14.9}, {2.6, 7.4}, {2.6, 7.4}, {2.8, 4.7}};
-    constexpr int simds = 1024, warm = 2 * cascade_halo(kCascadeSteps);
+    constexpr int warm = 2 * cascade_halo(kCascadeSteps);
     const int es = dtype == 0 ? 8 : (dtype == 3 ? 2 : 4);
     const double sites = (double)nx * ny;
     // 18 planes of the state pass the caches at 5.2 bytes per ps from HBM;
@@ -474,14 +505,14 @@ CascadeShape cascade_shape(int dtype, int nx, int ny)
     const double bytes_per_us = sites * 18 * es > 2.0e8 ? 5.2e6 : 1.0e7;
     CascadeShape best;
     double t_best = kCascadeSteps * (two_step[dtype][0] + two_step[dtype][1] * sites * 1e-6);
-    for (const Cost& c : costs) {
+    for (const CascadeCost& c : kCosts) {
         if (c.dtype != dtype) continue;
         const int w = cascade_cols(c.vx, kCascadeSteps, es), strips = (nx + w - 1) / w;
         for (int h = 6; h < ny + 4 && h < 256; h += 4) {
             const int chunks = (ny + h - 1) / h;
-            const double waves = (double)strips * chunks, slots = (double)simds * c.waves;
+            const double waves = (double)strips * chunks, slots = (double)kSimds * c.waves;
             const int rounds = (int)(waves / slots);
-            const int left = (int)((waves - rounds * slots + simds - 1) / simds);
+            const int left = (int)((waves - rounds * slots + kSimds - 1) / kSimds);
             const double full = c.waves * c.shared > c.alone ? c.waves * c.shared : c.alone;
             const double last = left == 0 ? 0 : (left * c.shared > c.alone ? left * c.shared : c.alone);
             const double work = 1.0 + (h + warm) * (rounds * full + last);
@@ -495,6 +526,74 @@ CascadeShape cascade_shape(int dtype, int nx, int ny)
         }
     }
     return best;
+}
+
+// The same for a batch, with the times and the two-step kernel's measured on
+// pools of 4 to 50 lattices of 0.09 to 24 M sites: a row takes longer there
+// (more strips are edges). Two-step against cascade, us per step: FP32 0.34 M
+// sites 7.3 and 6.6, 0.74 M 10.4 and 8.4, 11.4 M 108.6 and 56.4, 24.5 M 207
+// and 110; FP64 0.34 M 9.1 and 9.0, 2.3 M 45.0 and 23.4, 11.4 M 184 and 98.
+CascadeShape cascade_batch_shape(int dtype, const int* nx, const int* ny, int count)
+{
+    static const CascadeCost costs[] = {{0, 1, 2, 1.35, 1.10}, {1, 1, 3, 1.00, 0.66}, {1, 2, 2, 1.55, 1.25},
+                                        {2, 1, 3, 0.85, 0.58}, {2, 2, 2, 1.35, 1.10}};
+    static const double two_step[3][2] = {{3.5, 16.0}, {4.2, 9.0}, {4.2, 9.0}};
+    static const int heights[] = {6, 10, 14, 18, 22, 26, 34, 42, 50, 58, 74, 90, 130};
+    constexpr int warm = 2 * cascade_halo(kCascadeSteps);
+    CascadeShape best;
+    if (dtype == 3) return best;
+    const int es = dtype == 0 ? 8 : 4;
+    double sites = 0;
+    for (int k = 0; k < count; ++k) sites += (double)nx[k] * ny[k];
+    const double bytes_per_us = sites * 18 * es > 2.0e8 ? 5.2e6 : 1.0e7;
+    // near a tie the two-step kernel, whose tiles are smaller
+    double t_best = 0.96 * kCascadeSteps * (two_step[dtype][0] + two_step[dtype][1] * sites * 1e-6);
+    for (const CascadeCost& c : costs) {
+        if (c.dtype != dtype) continue;
+        const int w = cascade_cols(c.vx, kCascadeSteps, es);
+        for (const int h : heights) {
+            double waves = 0;
+            for (int k = 0; k < count; ++k) waves += (double)((nx[k] + w - 1) / w) * ((ny[k] + h - 1) / h);
+            const double slots = (double)kSimds * c.waves;
+            const int rounds = (int)(waves / slots);
+            const int left = (int)((waves - rounds * slots + kSimds - 1) / kSimds);
+            const double full = c.waves * c.shared > c.alone ? c.waves * c.shared : c.alone;
+            const double last = left == 0 ? 0 : (left * c.shared > c.alone ? left * c.shared : c.alone);
+            const double work = 2.0 + (h + warm) * (rounds * full + last);
+            const double bytes = 9.0 * es * sites * (1.15 * (h + warm) / h + 1);
+            const double t = work > bytes / bytes_per_us ? work : bytes / bytes_per_us;
+            if (t < t_best) {
+                t_best = t;
+                best.vx = c.vx;
+                best.h = h;
+            }
+        }
+    }
+    return best;
+}
+
+template <class T, bool SHIFT, int VX, int MW>
+static hipError_t launch_batch_cascade_t(const BatchLat* lats, const int* item_lat, int nitems, int p, hipStream_t st)
+{
+    const int grid = (nitems + 31) / 32 * 32;
+    if (nitems <= 0) return hipSuccess;
+    if (!grid_fits(grid, 64)) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((batch_cascade_kernel<T, SHIFT, VX, kCascadeSteps, MW>), dim3(grid), dim3(64), 0, st, lats,
+                       item_lat, nitems, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_cascade(int dtype, int vx, const BatchLat* lats, const int* item_lat, int nitems, int p,
+                                hipStream_t st)
+{
+    switch (dtype * 8 + vx) {
+    case 0 * 8 + 1: return launch_batch_cascade_t<double, false, 1, 2>(lats, item_lat, nitems, p, st);
+    case 1 * 8 + 1: return launch_batch_cascade_t<float, false, 1, 3>(lats, item_lat, nitems, p, st);
+    case 1 * 8 + 2: return launch_batch_cascade_t<float, false, 2, 2>(lats, item_lat, nitems, p, st);
+    case 2 * 8 + 1: return launch_batch_cascade_t<float, true, 1, 3>(lats, item_lat, nitems, p, st);
+    case 2 * 8 + 2: return launch_batch_cascade_t<float, true, 2, 2>(lats, item_lat, nitems, p, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <class T, bool SHIFT, int VX, int MW> static hipError_t launch_cascade_t(const StepTile& t, hipStream_t st)

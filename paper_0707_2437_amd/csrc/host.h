@@ -45,6 +45,10 @@ hipError_t launch_batch2(int dtype, int vx, int nw, bool nts, const BatchLat* la
 hipError_t launch_cascade(int dtype, int vx, const StepTile& t, hipStream_t st);
 // b.ns steps per launch on small lattices (block.hip).
 hipError_t launch_block(int dtype, const BlockShape& b, const StepTile& t, const BlockInlet* inlet, hipStream_t st);
+// Cascade pass p of a batch (descriptors with the strips and chunks of
+// cascade_cols, nsteps counting passes).
+hipError_t launch_batch_cascade(int dtype, int vx, const BatchLat* lats, const int* item_lat, int nitems, int p,
+                                hipStream_t st);
 hipError_t launch_ghosts(int dtype, void* s, const Geom& g, hipStream_t st);
 hipError_t launch_init(int dtype, void* s, const Geom& g, const double* rho, const double* ux, const double* uy,
                        double eqs, hipStream_t st);

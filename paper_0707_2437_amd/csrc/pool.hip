@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "arena.h"
+#include "cascade.h"
 #include "host.h"
 #include "tune.h"
 
@@ -48,10 +49,18 @@ struct DeviceAlloc {
 using SlotArena = lbm::Arena<DeviceAlloc>;
 
 struct GraphEntry {
-    int nsteps_max = 0, nitems = 0, vx = 0, nw = 0, nts = 0, ch = 0, two = 0;
+    // single- or two-step launches, then cascade passes
+    int nfirst = 0, nitems = 0, vx = 0, nw = 0, nts = 0, ch = 0, two = 0;
+    int deep_vx = 0, deep_passes = 0, deep_items = 0, deep_lats_at = 0;
     const BatchLat* lats = nullptr;
     const int* items = nullptr;
     hipGraphExec_t exec = nullptr;
+    bool same(const GraphEntry& o) const
+    {
+        return nfirst == o.nfirst && nitems == o.nitems && vx == o.vx && nw == o.nw && nts == o.nts && ch == o.ch &&
+               two == o.two && deep_vx == o.deep_vx && deep_passes == o.deep_passes && deep_items == o.deep_items &&
+               deep_lats_at == o.deep_lats_at && lats == o.lats && items == o.items;
+    }
 };
 
 }  // namespace
@@ -115,6 +124,10 @@ struct lbm_pool {
     std::vector<BatchLat> h_lats;
     std::vector<int> h_items;
     std::vector<GraphEntry> graphs;
+    // Cascade passes of the call being built: their descriptors and items
+    // follow the others' in h_lats and h_items.
+    int deep_vx = 0, deep_passes = 0, deep_lats_at = 0, deep_items_at = 0;
+    std::vector<int> sizes;
 };
 
 namespace {
@@ -141,22 +154,32 @@ void advance(Slot& S, int n, int two)
     S.t += n;
 }
 
+// ... or with the remainder of four in two-step passes and the rest in
+// cascade passes of four steps.
+void advance_deep(Slot& S, int n)
+{
+    S.ph = (int)((S.ph + (n % kCascadeSteps + 1) / 2 + n / kCascadeSteps + n) & 1);
+    S.t += n;
+}
+
 // The dtype's default tile of the batched kernels (from the batched
 // sweeps): the two-step tile where it is faster (16 waves, vx = 1 for FP64
 // and 2 for FP32 and FP32-shifted, as for single lattices), else (FP16) the
 // single-step vertical stack of 8 waves with vx = 4; non-temporal stores.
-void set_default_tile(lbm_pool* P)
+struct PoolTile {
+    int vx, nw, nts, two;
+};
+PoolTile default_pool_tile(int dtype)
 {
-    P->nts = 1;
-    if (P->dtype != LBM_F16S) {
-        P->two = 1;
-        P->nw = 16;
-        P->vx = P->dtype == LBM_F64 ? 1 : 2;
-    } else {
-        P->two = 0;
-        P->nw = 8;
-        P->vx = P->dtype == LBM_F16S ? 4 : 2;
-    }
+    if (dtype == LBM_F16S) return {4, 8, 1, 0};
+    return {dtype == LBM_F64 ? 1 : 2, 16, 1, 1};
+}
+// Whether a shape is the dtype's two-step default, which takes cascade
+// passes where they are faster.
+bool is_deep_tile(int dtype, int vx, int nw, int nts, int two)
+{
+    const PoolTile d = default_pool_tile(dtype);
+    return d.two && two && vx == d.vx && nw == d.nw && nts == d.nts;
 }
 
 void drop_graphs(lbm_pool* P)
@@ -239,16 +262,19 @@ void add_lattice(lbm_pool* P, BatchLat b)
     P->h_lats.push_back(b);
 }
 
-// Run the batch described by h_lats / h_items (already built) for nmax steps.
+// Run the batch described by h_lats / h_items (already built): nmax steps of
+// the first deep_lats_at lattices, then deep_passes cascade passes of the
+// others.
 hipError_t run_batch(lbm_pool* P, int nmax)
 {
-    const int nlat = (int)P->h_lats.size(), nitems = (int)P->h_items.size();
-    hipError_t e = ensure_cap(P, nlat, nitems);
+    const int nlat = (int)P->h_lats.size(), nitems = P->deep_items_at;
+    const int all_items = (int)P->h_items.size(), deep_items = all_items - nitems;
+    hipError_t e = ensure_cap(P, nlat, all_items);
     if (e != hipSuccess) return e;
     e = hipMemcpyAsync(P->d_lats, P->h_lats.data(), sizeof(BatchLat) * (size_t)nlat, hipMemcpyHostToDevice,
                        P->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(P->d_items, P->h_items.data(), sizeof(int) * (size_t)nitems, hipMemcpyHostToDevice,
+        e = hipMemcpyAsync(P->d_items, P->h_items.data(), sizeof(int) * (size_t)all_items, hipMemcpyHostToDevice,
                            P->stream);
     if (e != hipSuccess) return e;
     const bool nts = P->nts != 0;
@@ -257,20 +283,36 @@ hipError_t run_batch(lbm_pool* P, int nmax)
                                                  (nmax + 1) / 2, P->max_grid, P->xcd_chunk, P->d_bar, P->stream)
                       : launch_batch(P->dtype, P->vx, P->nw, nts, true, P->d_lats, P->d_items, nitems, nmax,
                                      P->max_grid, P->xcd_chunk, P->d_bar, P->stream);
-    // launch k of the call: step k, or two-step pass k
-    const int nlaunch = P->two ? (nmax + 1) / 2 : nmax;
+    // launch k of the call: step k, or two-step pass k; then the cascade passes
+    const int nfirst = nitems == 0 ? 0 : (P->two ? (nmax + 1) / 2 : nmax);
+    const int nlaunch = nfirst + P->deep_passes;
     auto launch_k = [&](int k) {
+        if (k >= nfirst)
+            return launch_batch_cascade(P->dtype, P->deep_vx, P->d_lats + P->deep_lats_at, P->d_items + nitems,
+                                        deep_items, k - nfirst, P->stream);
         return P->two ? launch_batch2(P->dtype, P->vx, P->nw, nts, P->d_lats, P->d_items, nitems, k, P->xcd_chunk,
                                       P->stream)
                       : launch_batch(P->dtype, P->vx, P->nw, nts, false, P->d_lats, P->d_items, nitems, k, 0,
                                      P->xcd_chunk, nullptr, P->stream);
     };
     if (P->mode == LBM_POOL_GRAPH) {
+        GraphEntry key;
+        key.nfirst = nfirst;
+        key.nitems = nitems;
+        key.vx = P->vx;
+        key.nw = P->nw;
+        key.nts = P->nts;
+        key.ch = P->xcd_chunk;
+        key.two = P->two;
+        key.deep_vx = P->deep_vx;
+        key.deep_passes = P->deep_passes;
+        key.deep_items = deep_items;
+        key.deep_lats_at = P->deep_lats_at;
+        key.lats = P->d_lats;
+        key.items = P->d_items;
         GraphEntry* ge = nullptr;
         for (auto& g : P->graphs)
-            if (g.nsteps_max == nmax && g.nitems == nitems && g.vx == P->vx && g.nw == P->nw && g.nts == P->nts &&
-                g.ch == P->xcd_chunk && g.two == P->two && g.lats == P->d_lats && g.items == P->d_items)
-                ge = &g;
+            if (key.same(g)) ge = &g;
         if (!ge) {
             // Capture the call's grouped launches once; replays re-read the
             // descriptors, which are refreshed above before every replay.
@@ -289,14 +331,56 @@ hipError_t run_batch(lbm_pool* P, int nmax)
                 (void)hipGraphExecDestroy(P->graphs.front().exec);
                 P->graphs.erase(P->graphs.begin());
             }
-            P->graphs.push_back(
-                GraphEntry{nmax, nitems, P->vx, P->nw, P->nts, P->xcd_chunk, P->two, P->d_lats, P->d_items, exec});
+            key.exec = exec;
+            P->graphs.push_back(key);
             ge = &P->graphs.back();
         }
         return hipGraphLaunch(ge->exec, P->stream);
     }
     for (int k = 0; k < nlaunch && e == hipSuccess; ++k) e = launch_k(k);
     return e;
+}
+
+// The cascade passes of a call that advances the listed slots by nsteps
+// (vx = 0: none): with the dtype's default tile, grouped or graph launches,
+// for the lattices that take at least one pass of four steps.
+CascadeShape pool_cascade(lbm_pool* P, const int* slots, const int* nsteps, int count)
+{
+    if (P->mode == LBM_POOL_PERSISTENT || !is_deep_tile(P->dtype, P->vx, P->nw, P->nts, P->two)) return {};
+    P->sizes.clear();
+    for (int d = 0; d < 2; ++d)
+        for (int k = 0; k < count; ++k) {
+            const Slot& S = P->slots[slots[k]];
+            if (nsteps[k] < kCascadeSteps) continue;
+            if (S.g.rs != 9LL * S.g.pitch) return {};  // plane-major: past 32-bit offsets
+            P->sizes.push_back(d == 0 ? S.nx : S.ny);
+        }
+    const int n = (int)P->sizes.size() / 2;
+    if (n == 0) return {};
+    return cascade_batch_shape(P->dtype, P->sizes.data(), P->sizes.data() + n, n);
+}
+
+// Append the descriptor of slot S for `passes` cascade passes, its items one
+// wave each.
+void add_cascade(lbm_pool* P, const Slot& S, const CascadeShape& c, int passes, long long buffer_t0)
+{
+    BatchLat b{};
+    b.tile = slot_tile(S, P->vx, P->nw, P->two);
+    const int w = cascade_cols(c.vx, kCascadeSteps, P->esize);
+    // chunks of even height, a whole number of the kernel's turns of four rows
+    const int chunks = (S.ny + c.h - 1) / c.h;
+    b.tile.h = ((S.ny + chunks - 1) / chunks + 1) / 4 * 4 + 2;
+    b.tile.nstrips = (S.nx + w - 1) / w;
+    b.tile.nchunks = (S.ny + b.tile.h - 1) / b.tile.h;
+    b.t0 = buffer_t0;
+    b.nsteps = passes;
+    b.ntiles = b.tile.nstrips * b.tile.nchunks;
+    b.per_item = 1;
+    b.item_begin = (int)P->h_items.size() - P->deep_items_at;
+    const int l = (int)P->h_lats.size() - P->deep_lats_at;
+    for (int k = 0; k < b.ntiles; ++k) P->h_items.push_back(l);
+    P->h_lats.push_back(b);
+    P->deep_passes = std::max(P->deep_passes, passes);
 }
 
 }  // namespace
@@ -319,7 +403,11 @@ lbm_pool* lbm_pool_create(size_t budget_bytes, int dtype)
     P->dtype = dtype;
     P->esize = esize_of(dtype);
     P->budget = budget_bytes;
-    set_default_tile(P);
+    const PoolTile tile = default_pool_tile(dtype);
+    P->vx = tile.vx;
+    P->nw = tile.nw;
+    P->nts = tile.nts;
+    P->two = tile.two;
     if (const char* ev = std::getenv("LBM_XCD_CHUNK")) {  // experiments: items per XCD chunk
         const int v = std::atoi(ev);
         if (v >= 0 && v <= 4096) P->xcd_chunk = v;
@@ -457,26 +545,47 @@ int lbm_pool_init_device(lbm_pool* P, int slot, const double* rho, const double*
 
 // The descriptors and work items of a batched call into P->h_lats and
 // P->h_items (host vectors whose capacity is kept from call to call);
-// *nmax = the largest step count.
-static int build_batch(lbm_pool* P, const int* slots, const int* nsteps, int count, int* nmax)
+// *nmax = the largest step count of the single- or two-step launches. deep:
+// the call may take cascade passes, and *took tells whether it does; the
+// slots' remainders of four go to the two-step launches before them.
+static int build_batch(lbm_pool* P, const int* slots, const int* nsteps, int count, int* nmax, bool deep, bool* took)
 {
     if (!P || count < 0 || (count > 0 && (!slots || !nsteps))) return LBM_EINVAL;
     P->h_lats.clear();
     P->h_items.clear();
+    P->deep_vx = P->deep_passes = 0;
     *nmax = 0;
+    *took = false;
     for (int k = 0; k < count; ++k) {
         Slot* S = slot_of(P, slots[k]);
         if (!S || nsteps[k] < 0) return LBM_EINVAL;
         if (!S->ready) return LBM_ESTATE;
         for (int j = 0; j < k; ++j)
             if (slots[j] == slots[k]) return LBM_EINVAL;  // a slot listed twice
-        if (nsteps[k] == 0) continue;
+    }
+    const CascadeShape c = deep ? pool_cascade(P, slots, nsteps, count) : CascadeShape{};
+    for (int k = 0; k < count; ++k) {
+        const int n = c.vx ? nsteps[k] % kCascadeSteps : nsteps[k];
+        if (n == 0) continue;
+        const Slot& S = P->slots[slots[k]];
         BatchLat b{};
-        b.tile = slot_tile(*S, P->vx, P->nw, P->two);
-        b.t0 = buffer_time(*S);
-        b.nsteps = nsteps[k];
+        b.tile = slot_tile(S, P->vx, P->nw, P->two);
+        b.t0 = buffer_time(S);
+        b.nsteps = n;
         add_lattice(P, b);
-        *nmax = std::max(*nmax, nsteps[k]);
+        *nmax = std::max(*nmax, n);
+    }
+    P->deep_lats_at = (int)P->h_lats.size();
+    P->deep_items_at = (int)P->h_items.size();
+    if (c.vx) {
+        *took = true;
+        P->deep_vx = c.vx;
+        for (int k = 0; k < count; ++k) {
+            if (nsteps[k] < kCascadeSteps) continue;
+            const Slot& S = P->slots[slots[k]];
+            const int left = nsteps[k] % kCascadeSteps;
+            add_cascade(P, S, c, nsteps[k] / kCascadeSteps, buffer_time(S) + (left + 1) / 2);
+        }
     }
     return LBM_OK;
 }
@@ -484,18 +593,23 @@ static int build_batch(lbm_pool* P, const int* slots, const int* nsteps, int cou
 int lbm_pool_step(lbm_pool* P, const int* slots, const int* nsteps, int count)
 {
     int nmax = 0;
-    const int st = build_batch(P, slots, nsteps, count, &nmax);
+    bool deep = false;
+    const int st = build_batch(P, slots, nsteps, count, &nmax, true, &deep);
     if (st != LBM_OK || P->h_lats.empty()) return st;
     hipError_t e = run_batch(P, nmax);
     if (e != hipSuccess) return status_of(e);
-    for (int k = 0; k < count; ++k) advance(P->slots[slots[k]], nsteps[k], P->two);
+    for (int k = 0; k < count; ++k) {
+        if (deep) advance_deep(P->slots[slots[k]], nsteps[k]);
+        else advance(P->slots[slots[k]], nsteps[k], P->two);
+    }
     return LBM_OK;
 }
 
 int lbm_pool_step_noalloc(lbm_pool* P, const int* slots, const int* nsteps, int count)
 {
     int nmax = 0;
-    const int st = build_batch(P, slots, nsteps, count, &nmax);
+    bool deep = false;
+    const int st = build_batch(P, slots, nsteps, count, &nmax, false, &deep);
     if (st != LBM_OK || P->h_lats.empty()) return st;
     const int nlat = (int)P->h_lats.size(), nitems = (int)P->h_items.size();
     if (nlat > kNoAllocLattices || nitems > kNoAllocItems) return LBM_EINVAL;
@@ -678,29 +792,50 @@ int lbm_pool_autotune(lbm_pool* P, const int* slots, int count, int reps, int us
     if (pers)  // 4-wave tiles (2 rows each) take one atomic per 2 rows: far slower persistent, and slow to time
         cands.erase(std::remove_if(cands.begin(), cands.end(), [](const TileCand& k) { return k.nw < 8; }),
                     cands.end());
-    // Every candidate is timed over two steps without advancing any slot:
-    // two batched launches at step 0 of a 1-step call (each reads each
-    // slot's current buffer and writes the other; a persistent launch of
-    // one step in persistent mode), or one two-step pass of a 2-step call
-    // (reads the current buffer, writes the other). The
+    // Every candidate is timed over four steps without advancing any slot:
+    // four batched launches at step 0 of a 1-step call (each reads each
+    // slot's current buffer and writes the other; persistent launches of
+    // one step in persistent mode), two two-step passes of a 2-step call
+    // (read the current buffer, write the other), or the cascade pass that a
+    // 4-step call with that tile takes. The
     // descriptors and the item map of a shape are built and uploaded by its
     // first (untimed) launch only, so that the timed launches measure the
     // kernel and not the host work, which grows with the number of items.
     TileCand built{};
     bool have_built = false;
     int nitems = 0;
+    CascadeShape four;
+    {
+        const PoolTile d = default_pool_tile(P->dtype);
+        const PoolTile now = {P->vx, P->nw, P->nts, P->two};
+        P->vx = d.vx;
+        P->nw = d.nw;
+        P->nts = d.nts;
+        P->two = d.two;
+        const std::vector<int> steps(count, kCascadeSteps);
+        four = pool_cascade(P, slots, steps.data(), count);
+        P->vx = now.vx;
+        P->nw = now.nw;
+        P->nts = now.nts;
+        P->two = now.two;
+    }
     auto launch = [&](const TileCand& k) -> hipError_t {
         const int two = (k.flags & LBM_TILE_TWO_STEP) ? 1 : 0;
         const bool nts = (k.flags & LBM_TILE_NT_STORE) != 0;
+        const CascadeShape deep = is_deep_tile(P->dtype, k.vx, k.nw, nts, two) ? four : CascadeShape{};
         auto go = [&]() {
-            if (two && pers)
-                return launch_batch2_persistent(P->dtype, k.vx, k.nw, nts, P->d_lats, P->d_items, nitems, 1,
-                                                P->max_grid, k.ch, P->d_bar, P->stream);
-            if (two) return launch_batch2(P->dtype, k.vx, k.nw, nts, P->d_lats, P->d_items, nitems, 0, k.ch, P->stream);
+            if (deep.vx) return launch_batch_cascade(P->dtype, deep.vx, P->d_lats, P->d_items, nitems, 0, P->stream);
             hipError_t ge = hipSuccess;
-            for (int r = 0; r < 2 && ge == hipSuccess; ++r)
-                ge = launch_batch(P->dtype, k.vx, k.nw, nts, pers, P->d_lats, P->d_items, nitems, pers ? 1 : 0,
-                                  pers ? P->max_grid : 0, k.ch, pers ? P->d_bar : nullptr, P->stream);
+            for (int r = 0; r < (two ? 2 : 4) && ge == hipSuccess; ++r) {
+                if (two && pers)
+                    ge = launch_batch2_persistent(P->dtype, k.vx, k.nw, nts, P->d_lats, P->d_items, nitems, 1,
+                                                  P->max_grid, k.ch, P->d_bar, P->stream);
+                else if (two)
+                    ge = launch_batch2(P->dtype, k.vx, k.nw, nts, P->d_lats, P->d_items, nitems, 0, k.ch, P->stream);
+                else
+                    ge = launch_batch(P->dtype, k.vx, k.nw, nts, pers, P->d_lats, P->d_items, nitems, pers ? 1 : 0,
+                                      pers ? P->max_grid : 0, k.ch, pers ? P->d_bar : nullptr, P->stream);
+            }
             return ge;
         };
         if (have_built && built.vx == k.vx && built.nw == k.nw && built.h == k.h &&
@@ -713,7 +848,12 @@ int lbm_pool_autotune(lbm_pool* P, const int* slots, int count, int reps, int us
         P->per_item = k.h;
         P->h_lats.clear();
         P->h_items.clear();
+        P->deep_lats_at = P->deep_items_at = 0;
         for (int j = 0; j < count; ++j) {
+            if (deep.vx) {
+                add_cascade(P, P->slots[slots[j]], deep, 1, buffer_time(P->slots[slots[j]]));
+                continue;
+            }
             BatchLat b{};
             b.tile = slot_tile(P->slots[slots[j]], k.vx, k.nw, two);
             b.t0 = buffer_time(P->slots[slots[j]]);
