@@ -117,6 +117,7 @@ struct lbm_pool {
     BatchLat* d_lats = nullptr;   // device descriptor array
     int* d_items = nullptr;       // device item -> lattice map
     unsigned* d_bar = nullptr;    // barrier state of the persistent kernel (kPoolBarWords words)
+    bool bar_used = false;        // a persistent launch was made since its flag was last read
     double* tot = nullptr;        // totals of lbm_pool_moments, in pinned host memory the device writes
     int cap = 0, item_cap = 0;
     int per_item = 1;             // tiles per work item
@@ -278,11 +279,13 @@ hipError_t run_batch(lbm_pool* P, int nmax)
                            P->stream);
     if (e != hipSuccess) return e;
     const bool nts = P->nts != 0;
-    if (P->mode == LBM_POOL_PERSISTENT)
+    if (P->mode == LBM_POOL_PERSISTENT) {
+        P->bar_used = true;
         return P->two ? launch_batch2_persistent(P->dtype, P->vx, P->nw, nts, P->d_lats, P->d_items, nitems,
                                                  (nmax + 1) / 2, P->max_grid, P->xcd_chunk, P->d_bar, P->stream)
                       : launch_batch(P->dtype, P->vx, P->nw, nts, true, P->d_lats, P->d_items, nitems, nmax,
                                      P->max_grid, P->xcd_chunk, P->d_bar, P->stream);
+    }
     // launch k of the call: step k, or two-step pass k; then the cascade passes
     const int nfirst = nitems == 0 ? 0 : (P->two ? (nmax + 1) / 2 : nmax);
     const int nlaunch = nfirst + P->deep_passes;
@@ -428,6 +431,7 @@ lbm_pool* lbm_pool_create(size_t budget_bytes, int dtype)
         delete P;
         return nullptr;
     }
+    lbm::staging_retain();
     P->stream = P->own;
     g_pool_error = LBM_OK;
     return P;
@@ -445,6 +449,7 @@ void lbm_pool_destroy(lbm_pool* P)
     if (P->tot) (void)hipHostFree(P->tot);
     if (P->own) (void)hipStreamDestroy(P->own);
     delete P;
+    lbm::staging_release();
 }
 
 size_t lbm_pool_slot_bytes(int nx, int ny, int dtype)
@@ -628,6 +633,7 @@ int lbm_pool_step_noalloc(lbm_pool* P, const int* slots, const int* nsteps, int 
                            P->stream);
     const bool nts = P->nts != 0;
     if (e == hipSuccess) {
+        if (P->mode == LBM_POOL_PERSISTENT) P->bar_used = true;
         if (P->mode == LBM_POOL_PERSISTENT && P->two) {
             e = launch_batch2_persistent(P->dtype, P->vx, P->nw, nts, d_lats, d_items, nitems, (nmax + 1) / 2,
                                          P->max_grid, P->xcd_chunk, P->d_bar, P->stream);
@@ -653,9 +659,11 @@ int lbm_pool_step_noalloc(lbm_pool* P, const int* slots, const int* nsteps, int 
 // of the launches after it, are incomplete), clearing the flag; else LBM_OK.
 static int take_barrier_error(lbm_pool* P)
 {
+    if (!P->bar_used) return LBM_OK;  // nothing to read: a copy of 4 bytes takes 15 us
     unsigned flag = 0;
     hipError_t e = hipMemcpy(&flag, P->d_bar + 2, sizeof(flag), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return status_of(e);
+    P->bar_used = false;
     if (!flag) return LBM_OK;
     unsigned zero[3] = {0, 0, 0};
     (void)hipMemcpy(P->d_bar, zero, sizeof(zero), hipMemcpyHostToDevice);
@@ -691,10 +699,9 @@ int lbm_pool_moments(lbm_pool* P, int slot, double* rho, double* ux, double* uy,
     if (e == hipSuccess)
         e = launch_moments(P->dtype, cur_buf(*S), S->g, dp[0], dp[1], dp[2], S->red,
                            done_word(S->buf, S->g, P->esize), P->tot, P->stream);
-    double* host[3] = {rho, ux, uy};
-    for (int c = 0; c < 3 && e == hipSuccess; ++c)
-        if (host[c]) e = hipMemcpyAsync(host[c], dp[c], n * sizeof(double), hipMemcpyDeviceToHost, P->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(P->stream);
+    const size_t bytes = n * sizeof(double);
+    const HostPart out[3] = {{rho, dp[0], bytes}, {ux, dp[1], bytes}, {uy, dp[2], bytes}};
+    if (e == hipSuccess) e = copy_out(out, 3, P->stream);
     if (e != hipSuccess) return status_of(e);
     const double tot[3] = {P->tot[0], P->tot[1], P->tot[2]};
     if (totals) std::memcpy(totals, tot, sizeof(tot));
@@ -723,8 +730,8 @@ int lbm_pool_get_f(lbm_pool* P, int slot, double* f)
     DevScratch d;
     hipError_t e = d.alloc(n, P->stream);
     if (e == hipSuccess) e = launch_get_f(P->dtype, cur_buf(*S), S->g, d.p, 0.0, P->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(f, d.p, n * sizeof(double), hipMemcpyDeviceToHost, P->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(P->stream);
+    const HostPart out = {f, d.p, n * sizeof(double)};
+    if (e == hipSuccess) e = copy_out(&out, 1, P->stream);
     if (e != hipSuccess) return status_of(e);
     return take_barrier_error(P);
 }
@@ -821,6 +828,7 @@ int lbm_pool_autotune(lbm_pool* P, const int* slots, int count, int reps, int us
     }
     auto launch = [&](const TileCand& k) -> hipError_t {
         const int two = (k.flags & LBM_TILE_TWO_STEP) ? 1 : 0;
+        if (pers) P->bar_used = true;
         const bool nts = (k.flags & LBM_TILE_NT_STORE) != 0;
         const CascadeShape deep = is_deep_tile(P->dtype, k.vx, k.nw, nts, two) ? four : CascadeShape{};
         auto go = [&]() {

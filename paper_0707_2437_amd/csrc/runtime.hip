@@ -294,6 +294,7 @@ lbm_lattice* lbm_create(int nx, int ny, double tau, double c2, int dtype)
         delete L;
         return nullptr;
     }
+    lbm::staging_retain();
     L->stream = L->own;
     L->buf_bytes = footprint(L->g, L->esize);
     e = hipMalloc(&L->buf, L->buf_bytes);
@@ -322,6 +323,7 @@ void lbm_destroy(lbm_lattice* L)
     if (L->field) (void)hipFree(L->field);
     if (L->own) (void)hipStreamDestroy(L->own);
     delete L;
+    lbm::staging_release();
 }
 
 int lbm_set_stream(lbm_lattice* L, void* s)
@@ -555,10 +557,9 @@ int lbm_moments(lbm_lattice* L, double* rho, double* ux, double* uy, double tota
     double* dp[3] = {rho ? d.p : nullptr, ux ? d.p + n : nullptr, uy ? d.p + 2 * n : nullptr};
     int st = lbm_moments_device(L, dp[0], dp[1], dp[2], totals);
     if (st != LBM_OK && st != LBM_ENONFINITE) return st;
-    double* host[3] = {rho, ux, uy};
-    for (int c = 0; c < 3 && e == hipSuccess; ++c)
-        if (host[c]) e = hipMemcpyAsync(host[c], dp[c], n * sizeof(double), hipMemcpyDeviceToHost, L->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
+    const size_t bytes = n * sizeof(double);
+    const HostPart out[3] = {{rho, dp[0], bytes}, {ux, dp[1], bytes}, {uy, dp[2], bytes}};
+    e = copy_out(out, 3, L->stream);
     return e != hipSuccess ? status_of(e) : st;
 }
 
@@ -570,8 +571,8 @@ int lbm_get_f(lbm_lattice* L, double* f)
     DevScratch d;
     hipError_t e = d.alloc(n, L->stream);
     if (e == hipSuccess) e = launch_get_f(L->dtype, L->cur, L->g, d.p, eq_shift(L->c2, L->model), L->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(f, d.p, n * sizeof(double), hipMemcpyDeviceToHost, L->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
+    const HostPart out = {f, d.p, n * sizeof(double)};
+    if (e == hipSuccess) e = copy_out(&out, 1, L->stream);
     return status_of(e);
 }
 
