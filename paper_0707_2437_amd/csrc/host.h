@@ -262,6 +262,10 @@ hipError_t copy_out(const HostPart* part, int nparts, hipStream_t st);
 // is destroyed.
 void staging_retain();
 void staging_release();
+// Pinned memory for the three totals of one lattice or pool, which holds its
+// share meanwhile.
+hipError_t totals_alloc(double** p);
+void totals_free(double* p);
 hipError_t scratch_alloc(void** p, size_t bytes, hipStream_t st);
 
 // Device staging memory of one host-array entry point: taken from a

@@ -420,18 +420,19 @@ lbm_pool* lbm_pool_create(size_t budget_bytes, int dtype)
     if (e == hipSuccess) e = noalloc_scratch(P->device, &noalloc_base);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&P->own, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipMalloc((void**)&P->d_bar, kPoolBarWords * sizeof(unsigned));
-    if (e == hipSuccess) e = hipHostMalloc((void**)&P->tot, 3 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent);
+    lbm::staging_retain();
+    if (e == hipSuccess) e = lbm::totals_alloc(&P->tot);
     if (e == hipSuccess) e = hipMemsetAsync(P->d_bar, 0, kPoolBarWords * sizeof(unsigned), P->own);
     if (e == hipSuccess) e = hipStreamSynchronize(P->own);
     if (e != hipSuccess) {
         g_pool_error = LBM_EDEVICE;
         if (P->d_bar) (void)hipFree(P->d_bar);
-        if (P->tot) (void)hipHostFree(P->tot);
+        lbm::totals_free(P->tot);
         if (P->own) (void)hipStreamDestroy(P->own);
         delete P;
+        lbm::staging_release();
         return nullptr;
     }
-    lbm::staging_retain();
     P->stream = P->own;
     g_pool_error = LBM_OK;
     return P;
@@ -446,7 +447,7 @@ void lbm_pool_destroy(lbm_pool* P)
     if (P->d_lats) (void)hipFree(P->d_lats);
     if (P->d_items) (void)hipFree(P->d_items);
     if (P->d_bar) (void)hipFree(P->d_bar);
-    if (P->tot) (void)hipHostFree(P->tot);
+    lbm::totals_free(P->tot);
     if (P->own) (void)hipStreamDestroy(P->own);
     delete P;
     lbm::staging_release();

@@ -20,7 +20,6 @@ struct lbm_lattice {
     int model;         // lbm_model
     Geom g;
     Coef coef;
-    size_t buf_bytes;
     void* buf;         // both population buffers
     void* cur;         // S of the current state (read by the next step)
     void* nxt;         // written by the next step
@@ -296,17 +295,17 @@ lbm_lattice* lbm_create(int nx, int ny, double tau, double c2, int dtype)
     }
     lbm::staging_retain();
     L->stream = L->own;
-    L->buf_bytes = footprint(L->g, L->esize);
-    e = hipMalloc(&L->buf, L->buf_bytes);
-    if (e == hipSuccess) e = hipMalloc((void**)&L->red, red_doubles(L->g) * sizeof(double));
-    if (e == hipSuccess) e = hipHostMalloc((void**)&L->tot, 3 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent);
-    if (e == hipSuccess) e = hipMemsetAsync(L->buf, 0, L->buf_bytes, L->stream);
+    const size_t red_at = (footprint(L->g, L->esize) + 63) / 64 * 64;  // one allocation: 30 us each
+    e = hipMalloc(&L->buf, red_at + red_doubles(L->g) * sizeof(double));
+    if (e == hipSuccess) e = lbm::totals_alloc(&L->tot);
+    if (e == hipSuccess) e = hipMemsetAsync(L->buf, 0, red_at, L->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
     if (e != hipSuccess) {
         g_last_error = e == hipErrorOutOfMemory ? LBM_ENOMEM : LBM_EDEVICE;
         lbm_destroy(L);
         return nullptr;
     }
+    L->red = (double*)((char*)L->buf + red_at);
     L->cur = L->buf;
     L->nxt = (char*)L->buf + (size_t)buffer_elems(L->g) * L->esize;
     g_last_error = LBM_OK;
@@ -318,8 +317,7 @@ void lbm_destroy(lbm_lattice* L)
     if (!L) return;
     if (L->own) (void)hipStreamSynchronize(L->stream);
     if (L->buf) (void)hipFree(L->buf);
-    if (L->red) (void)hipFree(L->red);
-    if (L->tot) (void)hipHostFree(L->tot);
+    lbm::totals_free(L->tot);
     if (L->field) (void)hipFree(L->field);
     if (L->own) (void)hipStreamDestroy(L->own);
     delete L;

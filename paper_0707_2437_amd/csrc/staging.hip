@@ -44,10 +44,14 @@ struct Ring {
     hipEvent_t ev[kSlots] = {};
 };
 
-// What outlives one call: at most kKeepRings rings, and kKeepScratch bytes of
-// device scratch per device, while any lattice or pool lives.
+// What outlives one call: at most kKeepRings rings, one page of totals and
+// kKeepScratch bytes of device scratch per device, while any lattice or pool
+// lives.
 std::mutex g_lock;
 int g_users = 0;
+constexpr int kLines = 64;           // of a page, 64 bytes each
+char* g_page = nullptr;
+unsigned long long g_lines_used = 0; // bit per line
 Ring g_kept[kKeepRings];
 hipMemPool_t g_scratch[kMaxDevices] = {};
 
@@ -246,9 +250,12 @@ void staging_retain()
 void staging_release()
 {
     Ring gone[kKeepRings];
+    char* page;
     {
         std::lock_guard<std::mutex> hold(g_lock);
         if (--g_users > 0) return;
+        page = g_page;
+        g_page = nullptr;
         for (int k = 0; k < kKeepRings; ++k) {
             gone[k] = g_kept[k];
             g_kept[k] = Ring();
@@ -257,6 +264,43 @@ void staging_release()
             if (m) (void)hipMemPoolTrimTo(m, 0);
     }
     for (Ring& r : gone) free_ring(r);
+    if (page) (void)hipHostFree(page);
+}
+
+// A line of the page, or memory of its own beyond kLines objects: an
+// allocation for each takes 15 us, 50 while others are alive.
+hipError_t totals_alloc(double** p)
+{
+    constexpr unsigned kind = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
+    *p = nullptr;
+    std::lock_guard<std::mutex> hold(g_lock);
+    if (!g_page) {
+        const hipError_t e = hipHostMalloc((void**)&g_page, (size_t)kLines * 64, kind);
+        if (e != hipSuccess) {
+            g_page = nullptr;
+            return e;
+        }
+    }
+    for (int k = 0; k < kLines; ++k)
+        if (!(g_lines_used >> k & 1)) {
+            g_lines_used |= 1ull << k;
+            *p = (double*)(g_page + (size_t)k * 64);
+            return hipSuccess;
+        }
+    return hipHostMalloc((void**)p, 64, kind);
+}
+
+void totals_free(double* p)
+{
+    if (!p) return;
+    {
+        std::lock_guard<std::mutex> hold(g_lock);
+        if (g_page && (char*)p >= g_page && (char*)p < g_page + (size_t)kLines * 64) {
+            g_lines_used &= ~(1ull << (((char*)p - g_page) / 64));
+            return;
+        }
+    }
+    (void)hipHostFree(p);
 }
 
 hipError_t scratch_alloc(void** p, size_t bytes, hipStream_t st)
