@@ -4,9 +4,9 @@
 
 namespace lbm {
 
-constexpr int kCascadeSteps = 4;  // steps per pass
+constexpr int kCascadeWaves = 4;  // of a team; a pass takes as many steps, or twice as many
 
-// A cascade wave advances a strip of 64 vx columns by ns steps of Eq. 5 in
+// A cascade team advances a strip of 64 vx columns by ns steps of Eq. 5 in
 // one pass over memory. Every step needs the neighbours' post-collision
 // values (one site away) and, for its density gradient, the neighbours'
 // densities; lanes take both from their neighbour lanes only, so a strip
@@ -30,13 +30,17 @@ constexpr int cascade_halo_lanes(int vx, int ns, int es)
 }
 constexpr int cascade_cols(int vx, int ns, int es) { return (64 - 2 * cascade_halo_lanes(vx, ns, es)) * vx; }
 
-// Shape of a lattice's cascade passes: columns per lane, rows per chunk; vx
-// = 0: two-step passes are faster.
+// Columns per lane.
+constexpr int cascade_vx(int dtype) { return dtype == 3 ? 4 : 2; }
+
+// Shape of a lattice's cascade passes: levels per wave (steps per pass /
+// kCascadeWaves), rows per chunk; levels = 0: other passes are faster.
 struct CascadeShape {
-    int vx = 0, h = 0;
+    int levels = 0, h = 0;
 };
-CascadeShape cascade_shape(int dtype, int nx, int ny);
-// The shape of a batch of lattices of the given sizes (nx[k] x ny[k]).
+// out[0]: four steps per pass, out[1]: eight.
+void cascade_shapes(int dtype, int nx, int ny, CascadeShape out[2]);
+// Four steps per pass of a batch of lattices of the given sizes (nx[k] x ny[k]).
 CascadeShape cascade_batch_shape(int dtype, const int* nx, const int* ny, int count);
 
 }  // namespace lbm

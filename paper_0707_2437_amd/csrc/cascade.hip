@@ -1,32 +1,36 @@
 // cascade.hip -- several steps of the variable-speed-of-sound D2Q9 step (Buick
 // & Cosgrove, Sec. 3 Eq. 5) per pass over memory, held in registers.
 //
-// Every 64-lane wave owns a strip of 64 * VX columns and walks down a chunk
+// A team of four waves owns a strip of 64 * VX columns and walks down a chunk
 // of rows. A row enters at level 0 from memory and falls through NS levels,
 // one step of Eq. 5 each; what leaves the last level is written. Level s
 // works two rows behind level s - 1: it relaxes a row as soon as the density
 // of the row below it is known, and hands the nine results, rounded to the
 // storage type, to level s + 1, which gathers a row from the results of
 // three consecutive rows (the planes with e_iy = 1 of the first, 0 of the
-// second, -1 of the third). Per level the wave keeps the populations of one
-// row, two rows of densities and the planes' rows that are still waited for;
-// x-neighbours come from the neighbour lanes (DPP wave shifts). There is no
-// LDS and no barrier. Every site's arithmetic is the single-step code of
+// second, -1 of the third). Each wave holds NL = NS / 4 levels; a row goes
+// from wave to wave through two LDS slots, with one barrier per row. Per level
+// a wave keeps the populations of one row, two rows of densities and the
+// planes' rows that are still waited for; x-neighbours come from the neighbour
+// lanes (DPP wave shifts). Every site's arithmetic is the single-step code of
 // step.h on the values a single step would load, so a pass gives the bits of
 // NS single steps.
 //
 // Bound: one load and one store of the state per NS steps, against 59
-// operations per site and step (77 with the FP32 form's conversions). At NS
-// = 4 the two are about even: FP32 at 4096^2 takes 285 us per pass, of which
-// the instructions alone need 195 us and the bare access pattern 262 us.
-// With NS = 2 and 3 the pass takes as long (270 and 299 us) and does less;
-// with NS = 5 the halo and the registers (one wave per SIMD) cost more than
-// they save (83 us per step against 71). The register file is the largest
-// on-chip memory (512 KB per CU against 160 KB of LDS), and 240 registers
-// per lane leave two waves per SIMD, enough here: a wave's loads for the
-// next row are in flight for the whole of a row's arithmetic.
-// Measured per step, the two-step kernel before and this one: FP32 4096^2
-// 121.7 and 71.3 us, FP64 4096^2 240.5 and 127.0 us.
+// operations per site and step (77 with the FP32 form's conversions, 80 with
+// the lane shifts), and the halo: 2 NS - 1 columns at each side of a strip
+// and as many rows before a chunk. FP32 at 4096^2, eight steps: 477 us per
+// pass, of which the instructions (halo included) need 400 and the bare
+// access pattern 262. With four steps the access pattern bounds the pass (280
+// us), so large lattices take eight; FP16 moves half the bytes and stays at
+// four. All levels in one wave, without LDS, was the form before: its
+// registers (250) allow two waves per SIMD and chunks have to be a quarter as
+// high to fill the GPU, so that the halo rows weigh four times as much.
+// Measured per step, two-step kernel / one wave / team: FP32 4096^2 121.7 /
+// 68.9 / 59.6 us, FP32S 121 / 71.7 / 50.1, FP64 240.5 / 127.7 / 111.6, FP16
+// 8192^2 389 / 217 / 186, FP32 1000 x 777 8.9 / 7.2 / 6.5, with a c2 field
+// 9.2 / 8.6 / 6.9. A team of eight waves of one level each: 61.1 us FP32, 53.5
+// FP32S, 112.2 FP64.
 #include <hip/hip_runtime.h>
 
 #include "cascade.h"
@@ -160,10 +164,13 @@ template <int VX> struct CascadeRow<_Float16, true, VX> {
 // densities w), the densities of the row above it (wp), and the planes of
 // its last results that wait for rows below: e_iy = 0 of the last row (z),
 // e_iy = 1 of the last two (up, by the row's parity).
+template <class R> struct CascadeWait {
+    R z[3], up[2][3];
+};
 template <class R, class C, int VX> struct CascadeLevel {
     R d[9];
     C w[VX], wp[VX];
-    R z[3], up[2][3];
+    CascadeWait<R> h;
 };
 
 constexpr unsigned kNoStore = 0x80000000u;  // past every row: the range check of a buffer store drops the lane
@@ -176,23 +183,31 @@ __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t rs, const V v, 
         __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), rs, voff, soff, aux);
     } else if constexpr (sizeof(V) == 4) {
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rs, voff, soff, aux);
-    } else {
-        static_assert(sizeof(V) == 8, "rows of up to two dwords per lane");
+    } else if constexpr (sizeof(V) == 8) {
         typedef unsigned u2 __attribute__((ext_vector_type(2)));
         __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), rs, voff, soff, aux);
+    } else {
+        static_assert(sizeof(V) == 16, "rows of up to four dwords per lane");
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), rs, voff, soff, aux);
     }
 }
 
-// One tile: NS steps of rows [chunk a.h, (chunk + 1) a.h) and the strip's
+// One wave's part of a tile (w: its place in the team; FIRST reads memory, LAST
+// writes it, in and outq are the LDS slots between): NS steps of rows [chunk a.h, (chunk + 1) a.h) and the strip's
 // inner columns. EDGE: a strip whose window reaches past the lattice's left
 // or right edge; its lanes load every element from its wrapped column
 // (Sec. 4: periodic in x) and store element by element.
-template <class T, bool SHIFT, int VX, int NS, bool FIELD, bool RC, bool EDGE>
-__device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src, void* dst, int strip, int chunk)
+template <class T, bool SHIFT, int VX, int NL, bool FIRST, bool LAST, bool FIELD, bool RC, bool EDGE>
+__device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src, void* dst, int strip, int chunk,
+                                             [[maybe_unused]] typename CascadeRow<T, SHIFT, VX>::Mem (*in)[9][64],
+                                             [[maybe_unused]] typename CascadeRow<T, SHIFT, VX>::Mem (*outq)[9][64],
+                                             int w)
 {
     using C = typename CompT<T>::type;
     using R = CascadeRow<T, SHIFT, VX>;
     using Mem = typename R::Mem;
+    constexpr int NW = kCascadeWaves, NS = NL * NW;
     constexpr unsigned es = sizeof(T);
     constexpr int H = cascade_halo(NS), HL = cascade_halo_lanes(VX, NS, es), W = cascade_cols(VX, NS, es);
     constexpr int WARM = 2 * H;  // rows that enter before the first row that is written
@@ -257,12 +272,12 @@ __device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src,
 
     // The rows' source coefficients (a c2 field), one row per level: level s
     // relaxes row r0 - 1 - 2 s of the lattice.
-    int fr[NS];
-    Pack<C, VX> af[NS] = {};
+    int fr[NL];
+    Pack<C, VX> af[NL] = {};
     auto load_field = [&]() {
         if constexpr (FIELD) {
 #pragma unroll
-            for (int s = 0; s < NS; ++s) {
+            for (int s = 0; s < NL; ++s) {
                 const char* row = (const char*)a.field + (size_t)fr[s] * a.fpitch * sizeof(C);
                 if constexpr (EDGE) {
 #pragma unroll
@@ -276,7 +291,7 @@ __device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src,
     };
     if constexpr (FIELD)
 #pragma unroll
-        for (int s = 0; s < NS; ++s) fr[s] = wrap(ylo - H - 1 - 2 * s);
+        for (int s = 0; s < NL; ++s) fr[s] = wrap(ylo - H - 1 - 2 * (w * NL + s));
 
     const int niter = nrow + WARM;
     // Write the kk-th row that leaves the last level. Every path issues the
@@ -307,11 +322,12 @@ __device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src,
         }
     };
 
-    CascadeLevel<R, C, VX> L[NS] = {};
-    Mem raw[9];
-    load(raw);
+    CascadeLevel<R, C, VX> L[NL] = {};
+    [[maybe_unused]] CascadeWait<R> gate = {};
+    [[maybe_unused]] Mem raw[9];
+    if constexpr (FIRST) load(raw);
     load_field();
-    {
+    if constexpr (LAST) {
         // writes nothing: the loop's first wait then counts the same
         // operations as the later ones
         const Mem none[9] = {};
@@ -323,25 +339,59 @@ __device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src,
     auto land = [&](const Mem (&m)[9], R (&r)[9]) {
         static_for<0, 9>([&](auto ic) { r[decltype(ic)::value] = R::of(m[decltype(ic)::value], decltype(ic)::value, cn); });
     };
+    // The next level's row, gathered from the results q of this row and the
+    // two before it.
+    auto gather = [&](auto parity, CascadeWait<R>& h, const R (&q)[9], R (&nd)[9]) {
+        constexpr int P = decltype(parity)::value;
+        nd[0] = h.z[0];
+        nd[1] = h.z[1].template shifted<1>();
+        nd[3] = h.z[2].template shifted<-1>();
+        nd[2] = h.up[P][0];
+        nd[5] = h.up[P][1].template shifted<1>();
+        nd[6] = h.up[P][2].template shifted<-1>();
+        nd[4] = q[4];
+        nd[7] = q[7].template shifted<-1>();
+        nd[8] = q[8].template shifted<1>();
+        h.z[0] = q[0];
+        h.z[1] = q[1];
+        h.z[2] = q[3];
+        h.up[P][0] = q[2];
+        h.up[P][1] = q[5];
+        h.up[P][2] = q[6];
+    };
+    auto meet = [&]() {
+        // LDS only: a full fence would wait for the next row's loads too
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
     // The kk-th row enters; P: its parity.
     auto iterate = [&](int kk, auto parity) {
         constexpr int P = decltype(parity)::value;
         R nd[9];
-        land(raw, nd);
-        Pack<C, VX> fa[NS];
-        static_for<0, NS>([&](auto sc) { fa[decltype(sc)::value] = af[decltype(sc)::value]; });
-        if (kk + 1 < niter) {
+        if constexpr (FIRST) {
+            land(raw, nd);
+        } else {
+            Mem m[9];
+            static_for<0, 9>([&](auto ic) { m[decltype(ic)::value] = in[P][decltype(ic)::value][lane]; });
+            R q[9];
+            land(m, q);
+            gather(parity, gate, q, nd);
+        }
+        Pack<C, VX> fa[NL];
+        static_for<0, NL>([&](auto sc) { fa[decltype(sc)::value] = af[decltype(sc)::value]; });
+        if (FIRST && kk + 1 < niter) {
             rm = r0;
             r0 = rp;
             rp = next(rp);
         }
         if constexpr (FIELD)
 #pragma unroll
-            for (int s = 0; s < NS; ++s) fr[s] = next(fr[s]);
-        load(raw);
+            for (int s = 0; s < NL; ++s) fr[s] = next(fr[s]);
+        if constexpr (FIRST) load(raw);
         load_field();
         __builtin_amdgcn_sched_barrier(0);  // the loads first, then the arithmetic they overlap with
-        static_for<0, NS>([&](auto sc) {
+        static_for<0, NL>([&](auto sc) {
             constexpr int s = decltype(sc)::value;
             auto& l = L[s];
             C nw[VX];
@@ -373,36 +423,26 @@ __device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src,
                 l.w[j] = nw[j];
             }
             static_for<0, 9>([&](auto ic) { l.d[decltype(ic)::value] = nd[decltype(ic)::value]; });
-            if constexpr (s + 1 < NS) {
-                // the row above the relaxed one, gathered for the next level
+            if constexpr (s + 1 < NL) {
                 R q[9];
                 land(f, q);
-                nd[0] = l.z[0];
-                nd[1] = l.z[1].template shifted<1>();
-                nd[3] = l.z[2].template shifted<-1>();
-                nd[2] = l.up[P][0];
-                nd[5] = l.up[P][1].template shifted<1>();
-                nd[6] = l.up[P][2].template shifted<-1>();
-                nd[4] = q[4];
-                nd[7] = q[7].template shifted<-1>();
-                nd[8] = q[8].template shifted<1>();
-                l.z[0] = q[0];
-                l.z[1] = q[1];
-                l.z[2] = q[3];
-                l.up[P][0] = q[2];
-                l.up[P][1] = q[5];
-                l.up[P][2] = q[6];
-            } else {
+                gather(parity, l.h, q, nd);
+            } else if constexpr (LAST) {
                 write(kk, f);
+            } else {
+                static_for<0, 9>([&](auto ic) { outq[P][decltype(ic)::value][lane] = f[decltype(ic)::value]; });
             }
         });
+        meet();
     };
     // Four rows per turn: a value lives for up to four rows in a level's
     // state, and with a shorter turn its registers would be copied.
+    for (int k = 0; k < w; ++k) meet();
     for (int kk = 0; kk < niter; kk += 4)
         static_for<0, 4>([&](auto u) {
             iterate(kk + decltype(u)::value, std::integral_constant<int, decltype(u)::value % 2>{});
         });
+    for (int k = w + 1; k < NW; ++k) meet();
 }
 
 // Ghost copies of a lattice's edge columns (columns -2, -1 hold nx - 2, nx - 1;
@@ -429,33 +469,59 @@ hipError_t launch_ghosts(int dtype, void* s, const Geom& g, hipStream_t st)
     return hipGetLastError();
 }
 
+// Between the waves of a team: the last two rows each hands to the next.
+template <class T, bool SHIFT, int VX> struct CascadeRing {
+    typename CascadeRow<T, SHIFT, VX>::Mem row[kCascadeWaves - 1][2][9][64];
+};
+
+// One wave of a team. The waves pass the same number of barriers: a wave's
+// first row is one barrier behind that of the wave before it.
+template <class T, bool SHIFT, int VX, int NL, bool FIELD, bool RC, bool EDGE>
+__device__ __forceinline__ void cascade_wave(const StepTile& a, const void* src, void* dst, int strip, int chunk,
+                                             CascadeRing<T, SHIFT, VX>& ring)
+{
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w == 0)
+        cascade_tile<T, SHIFT, VX, NL, true, false, FIELD, RC, EDGE>(a, src, dst, strip, chunk, nullptr, ring.row[0], 0);
+    else if (w == kCascadeWaves - 1)
+        cascade_tile<T, SHIFT, VX, NL, false, true, FIELD, RC, EDGE>(a, src, dst, strip, chunk, ring.row[w - 1], nullptr, w);
+    else
+        cascade_tile<T, SHIFT, VX, NL, false, false, FIELD, RC, EDGE>(a, src, dst, strip, chunk, ring.row[w - 1],
+                                                                      ring.row[w], w);
+}
+
 // MW: waves per SIMD the registers are held to.
-template <class T, bool SHIFT, int VX, int NS, int MW, bool FIELD>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MW, MW))) void cascade_kernel(StepTile a, int ntiles)
+template <class T, bool SHIFT, int VX, int NL, int MW, bool FIELD>
+__global__ __launch_bounds__(64 * kCascadeWaves) __attribute__((amdgpu_waves_per_eu(MW, MW))) void cascade_kernel(
+    StepTile a, int ntiles)
 {
     constexpr bool RC = ModelCentred<typename CompT<T>::type>::value;
-    constexpr int es = sizeof(T), W = cascade_cols(VX, NS, es), HL = cascade_halo_lanes(VX, NS, es);
+    constexpr int es = sizeof(T), NS = NL * kCascadeWaves, W = cascade_cols(VX, NS, es),
+                  HL = cascade_halo_lanes(VX, NS, es);
+    __shared__ CascadeRing<T, SHIFT, VX> ring;
     const int t = xcd_tile(blockIdx.x, gridDim.x, a.xcd_chunk);
     if (t >= ntiles) return;
     const int strip = t % a.nstrips, chunk = t / a.nstrips;
     const int x0 = strip * W - HL * VX;  // the strip's window
     if (x0 - 1 < 0 || x0 + 64 * VX + 1 > a.g.nx)
-        cascade_tile<T, SHIFT, VX, NS, FIELD, RC, true>(a, a.src, a.dst, strip, chunk);
+        cascade_wave<T, SHIFT, VX, NL, FIELD, RC, true>(a, a.src, a.dst, strip, chunk, ring);
     else
-        cascade_tile<T, SHIFT, VX, NS, FIELD, RC, false>(a, a.src, a.dst, strip, chunk);
+        cascade_wave<T, SHIFT, VX, NL, FIELD, RC, false>(a, a.src, a.dst, strip, chunk, ring);
 }
 
 // Batched form: pass p of every lattice of a batch (BatchLat in internal.h,
 // with nsteps counting cascade passes and t0 the buffer time at the first);
-// one wave per item, an item being one strip of one chunk, dealt to the XCDs
+// one team per item, an item being one strip of one chunk, dealt to the XCDs
 // four at a time (neighbouring strips share their halo's lines in an L2; one
 // run per XCD and single items measured within 2 % of it).
-template <class T, bool SHIFT, int VX, int NS, int MW>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MW, MW))) void batch_cascade_kernel(
+template <class T, bool SHIFT, int VX, int NL, int MW>
+__global__ __launch_bounds__(64 * kCascadeWaves) __attribute__((amdgpu_waves_per_eu(MW, MW))) void batch_cascade_kernel(
     const BatchLat* __restrict__ lats, const int* __restrict__ item_lat, int nitems, int p)
 {
     constexpr bool RC = ModelCentred<typename CompT<T>::type>::value;
-    constexpr int es = sizeof(T), W = cascade_cols(VX, NS, es), HL = cascade_halo_lanes(VX, NS, es);
+    constexpr int es = sizeof(T), NS = NL * kCascadeWaves, W = cascade_cols(VX, NS, es),
+                  HL = cascade_halo_lanes(VX, NS, es);
+    __shared__ CascadeRing<T, SHIFT, VX> ring;
     const int i = xcd_tile(blockIdx.x, gridDim.x, 4);
     if (i >= nitems) return;
     const BatchLat& L = lats[item_lat[i]];
@@ -467,158 +533,158 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MW, MW))) vo
     const int strip = t % L.tile.nstrips, chunk = t / L.tile.nstrips;
     const int x0 = strip * W - HL * VX;
     if (x0 - 1 < 0 || x0 + 64 * VX + 1 > L.tile.g.nx)
-        cascade_tile<T, SHIFT, VX, NS, false, RC, true>(L.tile, src, dst, strip, chunk);
+        cascade_wave<T, SHIFT, VX, NL, false, RC, true>(L.tile, src, dst, strip, chunk, ring);
     else
-        cascade_tile<T, SHIFT, VX, NS, false, RC, false>(L.tile, src, dst, strip, chunk);
+        cascade_wave<T, SHIFT, VX, NL, false, RC, false>(L.tile, src, dst, strip, chunk, ring);
 }
 
-// The time a row takes on MI355X, in us: `alone` for a wave that has its
-// SIMD to itself (the latency of the four levels' chain), `shared` per wave
-// where several share one (instruction issue); waves: per SIMD that the
-// registers allow.
+// The time a team takes per row on MI355X, in us, with one, two ... teams on
+// its CU (of as many as registers and LDS allow), from fits over lattices of
+// 400^2 to 4096^2 (within 10 % there).
 struct CascadeCost {
-    int dtype, vx, waves;
-    double alone, shared;
+    int dtype, levels, teams;
+    double row[4];
 };
-static const CascadeCost kCosts[] = {{0, 1, 2, 1.25, 1.10}, {1, 1, 3, 0.85, 0.62}, {1, 2, 2, 1.45, 1.20},
-                                     {2, 1, 3, 0.72, 0.55}, {2, 2, 2, 1.25, 1.05}, {3, 2, 3, 1.70, 1.25}};
-constexpr int kSimds = 1024;
+static const CascadeCost kCosts[] = {
+    {0, 1, 2, {0.78, 1.08}},       {0, 2, 1, {1.12}},
+    {1, 1, 4, {0.60, 0.72, 1.07, 1.39}}, {1, 2, 3, {0.82, 1.19, 1.75}},
+    {2, 1, 4, {0.53, 0.62, 1.00, 1.32}}, {2, 2, 3, {0.70, 1.03, 1.46}},
+    {3, 1, 3, {1.15, 1.40, 1.71}}};
+constexpr int kCus = 256;
 
-// Which shape, if any. A chunk of h rows takes h + 14 rows of work, so
-// few tall chunks waste least, but the GPU needs a wave on each of its 1024
-// SIMDs, and the last wave of an uneven count runs alone. The estimate counts
-// both with the times of CascadeCost, from fits over 14 lattice sizes of 64^2
-// to 4099 x 2731 (within 10 % there), with a floor for
-// the memory traffic. The two-step kernel takes t0 + t1 per million sites
-// and step. Measured at the crossing (FP32, us per step, two-step against
-// cascade): 512^2 4.5 and 4.9, 700^2 6.5 and 6.1, 1000 x 777 8.9 and 7.1,
-// 2048^2 33.3 and 22.1; FP64: 512^2 6.2 and 7.3, 700^2 10.5 and 8.3; FP16
-// 2048^2 21.6 and 23.5, 4099 x 2731 69.9 and 42.9.
-CascadeShape cascade_shape(int dtype, int nx, int ny)
+// A pass of `teams` teams of h rows: they fill the CUs in rounds, the last of
+// which holds fewer per CU.
+static double cascade_time(const CascadeCost& c, double teams, int h)
+{
+    const double slots = (double)kCus * c.teams;
+    const int rounds = (int)(teams / slots);
+    const int left = (int)((teams - rounds * slots + kCus - 1) / kCus);
+    const int rows = h + 2 * cascade_halo(c.levels * kCascadeWaves) + kCascadeWaves - 1;
+    return rows * (rounds * c.row[c.teams - 1] + (left ? c.row[left - 1] : 0.0));
+}
+
+// 18 planes of the state pass the caches at 5.2 bytes per ps from HBM; a state
+// that fits the 256 MB last-level cache is not bound by it.
+static double cascade_bytes_per_us(double state_bytes) { return state_bytes > 2.0e8 ? 5.2e6 : 1.0e7; }
+
+// Few tall chunks waste least on the halo, but the GPU needs a team on each
+// of its 256 CUs, and the last round of an uneven count runs half empty. The
+// estimate counts both, with a floor for the memory traffic. The two-step
+// kernel takes t0 + t1 per million sites and step. Measured, us per step,
+// two-step against four-step passes: FP32 400^2 4.1 and 4.5, 512^2 4.5 and
+// 4.8, 700^2 6.5 and 5.4, 1000 x 777 8.9 and 6.5; FP64 512^2 6.2 and 6.3, 700^2
+// 10.5 and 8.0. Four-step against eight-step: FP32 1000 x 777 6.5 and 7.6,
+// 2048^2 21.4 and 19.3, 4096^2 70.0 and 59.6; FP64 1000 x 777 10.5 and 10.8,
+// 2048^2 34.6 and 35.9, 4096^2 123.8 and 111.6.
+void cascade_shapes(int dtype, int nx, int ny, CascadeShape out[2])
 {
     static const double two_step[4][2] = {{2.4, 14.9}, {2.6, 7.4}, {2.6, 7.4}, {2.8, 4.7}};
-    constexpr int warm = 2 * cascade_halo(kCascadeSteps);
     const int es = dtype == 0 ? 8 : (dtype == 3 ? 2 : 4);
-    const double sites = (double)nx * ny;
-    // 18 planes of the state pass the caches at 5.2 bytes per ps from HBM;
-    // a state that fits the 256 MB last-level cache moves about twice as fast
-    const double bytes_per_us = sites * 18 * es > 2.0e8 ? 5.2e6 : 1.0e7;
-    CascadeShape best;
-    double t_best = kCascadeSteps * (two_step[dtype][0] + two_step[dtype][1] * sites * 1e-6);
-    for (const CascadeCost& c : kCosts) {
-        if (c.dtype != dtype) continue;
-        const int w = cascade_cols(c.vx, kCascadeSteps, es), strips = (nx + w - 1) / w;
-        for (int h = 6; h < ny + 4 && h < 256; h += 4) {
-            const int chunks = (ny + h - 1) / h;
-            const double waves = (double)strips * chunks, slots = (double)kSimds * c.waves;
-            const int rounds = (int)(waves / slots);
-            const int left = (int)((waves - rounds * slots + kSimds - 1) / kSimds);
-            const double full = c.waves * c.shared > c.alone ? c.waves * c.shared : c.alone;
-            const double last = left == 0 ? 0 : (left * c.shared > c.alone ? left * c.shared : c.alone);
-            const double work = 1.0 + (h + warm) * (rounds * full + last);
-            const double bytes = 9.0 * es * nx * (1.15 * chunks * (h + warm) + ny);
-            const double t = work > bytes / bytes_per_us ? work : bytes / bytes_per_us;
-            if (t < t_best) {
-                t_best = t;
-                best.vx = c.vx;
-                best.h = h;
+    const double sites = (double)nx * ny, per_us = cascade_bytes_per_us(sites * 18 * es);
+    // us per step of the best so far
+    double t_best = two_step[dtype][0] + two_step[dtype][1] * sites * 1e-6;
+    for (int levels = 1; levels <= 2; ++levels) {
+        out[levels - 1] = CascadeShape();
+        const int ns = levels * kCascadeWaves, warm = 2 * cascade_halo(ns);
+        for (const CascadeCost& c : kCosts) {
+            if (c.dtype != dtype || c.levels != levels) continue;
+            const int w = cascade_cols(cascade_vx(dtype), ns, es), strips = (nx + w - 1) / w;
+            for (int h = 6; h < ny + 4 && h < 400; h += 4) {
+                const int chunks = (ny + h - 1) / h;
+                const double work = 1.0 + cascade_time(c, (double)strips * chunks, h);
+                const double bytes = 9.0 * es * nx * (1.15 * chunks * (h + warm) + ny);
+                const double t = (work > bytes / per_us ? work : bytes / per_us) / ns;
+                if (t < t_best) {
+                    t_best = t;
+                    out[levels - 1] = {levels, h};
+                }
             }
         }
     }
-    return best;
 }
 
-// The same for a batch, with the times and the two-step kernel's measured on
-// pools of 4 to 50 lattices of 0.09 to 24 M sites: a row takes longer there
-// (more strips are edges). Two-step against cascade, us per step: FP32 0.34 M
-// sites 7.3 and 6.6, 0.74 M 10.4 and 8.4, 11.4 M 108.6 and 56.4, 24.5 M 207
-// and 110; FP64 0.34 M 9.1 and 9.0, 2.3 M 45.0 and 23.4, 11.4 M 184 and 98.
+// The four-step shape of a batch of lattices. Measured on pools of 4 to 60
+// lattices, two-step against four-step passes, us per step: FP32 0.33 M sites
+// 6.4 and 5.8, 0.86 M 11.6 and 6.9, 2.7 M 32.5 and 17.6, 8.8 M 82 and 43; FP64
+// 0.33 M 8.2 and 7.4, 0.86 M 17.6 and 10.4, 8.8 M 145 and 75.
 CascadeShape cascade_batch_shape(int dtype, const int* nx, const int* ny, int count)
 {
-    static const CascadeCost costs[] = {{0, 1, 2, 1.35, 1.10}, {1, 1, 3, 1.00, 0.66}, {1, 2, 2, 1.55, 1.25},
-                                        {2, 1, 3, 0.85, 0.58}, {2, 2, 2, 1.35, 1.10}};
     static const double two_step[3][2] = {{3.5, 16.0}, {4.2, 9.0}, {4.2, 9.0}};
-    static const int heights[] = {6, 10, 14, 18, 22, 26, 34, 42, 50, 58, 74, 90, 130};
-    constexpr int warm = 2 * cascade_halo(kCascadeSteps);
+    static const int heights[] = {6, 10, 14, 18, 22, 26, 30, 34, 42, 50, 58, 66, 74, 86, 98, 114, 130};
+    constexpr int warm = 2 * cascade_halo(kCascadeWaves);
     CascadeShape best;
     if (dtype == 3) return best;
-    const int es = dtype == 0 ? 8 : 4;
+    const int es = dtype == 0 ? 8 : 4, w = cascade_cols(cascade_vx(dtype), kCascadeWaves, es);
     double sites = 0;
     for (int k = 0; k < count; ++k) sites += (double)nx[k] * ny[k];
-    const double bytes_per_us = sites * 18 * es > 2.0e8 ? 5.2e6 : 1.0e7;
+    const double per_us = cascade_bytes_per_us(sites * 18 * es);
     // near a tie the two-step kernel, whose tiles are smaller
-    double t_best = 0.96 * kCascadeSteps * (two_step[dtype][0] + two_step[dtype][1] * sites * 1e-6);
-    for (const CascadeCost& c : costs) {
-        if (c.dtype != dtype) continue;
-        const int w = cascade_cols(c.vx, kCascadeSteps, es);
+    double t_best = 0.96 * kCascadeWaves * (two_step[dtype][0] + two_step[dtype][1] * sites * 1e-6);
+    for (const CascadeCost& c : kCosts) {
+        if (c.dtype != dtype || c.levels != 1) continue;
         for (const int h : heights) {
-            double waves = 0;
-            for (int k = 0; k < count; ++k) waves += (double)((nx[k] + w - 1) / w) * ((ny[k] + h - 1) / h);
-            const double slots = (double)kSimds * c.waves;
-            const int rounds = (int)(waves / slots);
-            const int left = (int)((waves - rounds * slots + kSimds - 1) / kSimds);
-            const double full = c.waves * c.shared > c.alone ? c.waves * c.shared : c.alone;
-            const double last = left == 0 ? 0 : (left * c.shared > c.alone ? left * c.shared : c.alone);
-            const double work = 2.0 + (h + warm) * (rounds * full + last);
+            double teams = 0;
+            for (int k = 0; k < count; ++k) teams += (double)((nx[k] + w - 1) / w) * ((ny[k] + h - 1) / h);
+            const double work = 2.0 + cascade_time(c, teams, h);
             const double bytes = 9.0 * es * sites * (1.15 * (h + warm) / h + 1);
-            const double t = work > bytes / bytes_per_us ? work : bytes / bytes_per_us;
+            const double t = work > bytes / per_us ? work : bytes / per_us;
             if (t < t_best) {
                 t_best = t;
-                best.vx = c.vx;
-                best.h = h;
+                best = {1, h};
             }
         }
     }
     return best;
 }
 
-template <class T, bool SHIFT, int VX, int MW>
+template <class T, bool SHIFT, int MW>
 static hipError_t launch_batch_cascade_t(const BatchLat* lats, const int* item_lat, int nitems, int p, hipStream_t st)
 {
-    const int grid = (nitems + 31) / 32 * 32;
+    const int grid = (nitems + 31) / 32 * 32, threads = 64 * kCascadeWaves;
     if (nitems <= 0) return hipSuccess;
-    if (!grid_fits(grid, 64)) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((batch_cascade_kernel<T, SHIFT, VX, kCascadeSteps, MW>), dim3(grid), dim3(64), 0, st, lats,
-                       item_lat, nitems, p);
+    if (!grid_fits(grid, threads)) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((batch_cascade_kernel<T, SHIFT, 2, 1, MW>), dim3(grid), dim3(threads), 0, st, lats, item_lat,
+                       nitems, p);
     return hipGetLastError();
 }
 
-hipError_t launch_batch_cascade(int dtype, int vx, const BatchLat* lats, const int* item_lat, int nitems, int p,
-                                hipStream_t st)
+hipError_t launch_batch_cascade(int dtype, const BatchLat* lats, const int* item_lat, int nitems, int p, hipStream_t st)
 {
-    switch (dtype * 8 + vx) {
-    case 0 * 8 + 1: return launch_batch_cascade_t<double, false, 1, 2>(lats, item_lat, nitems, p, st);
-    case 1 * 8 + 1: return launch_batch_cascade_t<float, false, 1, 3>(lats, item_lat, nitems, p, st);
-    case 1 * 8 + 2: return launch_batch_cascade_t<float, false, 2, 2>(lats, item_lat, nitems, p, st);
-    case 2 * 8 + 1: return launch_batch_cascade_t<float, true, 1, 3>(lats, item_lat, nitems, p, st);
-    case 2 * 8 + 2: return launch_batch_cascade_t<float, true, 2, 2>(lats, item_lat, nitems, p, st);
+    switch (dtype) {
+    case 0: return launch_batch_cascade_t<double, false, 2>(lats, item_lat, nitems, p, st);
+    case 1: return launch_batch_cascade_t<float, false, 4>(lats, item_lat, nitems, p, st);
+    case 2: return launch_batch_cascade_t<float, true, 4>(lats, item_lat, nitems, p, st);
     }
     return hipErrorInvalidValue;
 }
 
-template <class T, bool SHIFT, int VX, int MW> static hipError_t launch_cascade_t(const StepTile& t, hipStream_t st)
+template <class T, bool SHIFT, int VX, int NL, int MW, bool FIELD>
+static hipError_t launch_cascade_t(const StepTile& t, hipStream_t st)
 {
-    const int ntiles = t.nstrips * t.nchunks;
+    const int ntiles = t.nstrips * t.nchunks, threads = 64 * kCascadeWaves;
     const int q = t.xcd_chunk > 0 ? 8 * t.xcd_chunk : 8;
     const int grid = (ntiles + q - 1) / q * q;
-    if (!grid_fits(grid, 64)) return hipErrorInvalidConfiguration;
-    if (t.field)
-        hipLaunchKernelGGL((cascade_kernel<T, SHIFT, VX, kCascadeSteps, MW, true>), dim3(grid), dim3(64), 0, st, t, ntiles);
-    else
-        hipLaunchKernelGGL((cascade_kernel<T, SHIFT, VX, kCascadeSteps, MW, false>), dim3(grid), dim3(64), 0, st, t, ntiles);
+    if (!grid_fits(grid, threads)) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((cascade_kernel<T, SHIFT, VX, NL, MW, FIELD>), dim3(grid), dim3(threads), 0, st, t, ntiles);
     return hipGetLastError();
 }
 
-// vx: 1 or 2 columns per lane for 4-byte storage, 1 for FP64, 2 for FP16.
-hipError_t launch_cascade(int dtype, int vx, const StepTile& t, hipStream_t st)
+// levels: per wave; 2 (eight steps per pass) without a c2 field, whose rows
+// would take the registers past their limit, and not for FP16.
+hipError_t launch_cascade(int dtype, int levels, const StepTile& t, hipStream_t st)
 {
-    switch (dtype * 8 + vx) {
-    case 0 * 8 + 1: return launch_cascade_t<double, false, 1, 2>(t, st);
-    case 1 * 8 + 1: return launch_cascade_t<float, false, 1, 3>(t, st);
-    case 1 * 8 + 2: return launch_cascade_t<float, false, 2, 2>(t, st);
-    case 2 * 8 + 1: return launch_cascade_t<float, true, 1, 3>(t, st);
-    case 2 * 8 + 2: return launch_cascade_t<float, true, 2, 2>(t, st);
-    case 3 * 8 + 2: return launch_cascade_t<_Float16, true, 2, 3>(t, st);
+    switch (dtype * 4 + (t.field ? 2 : 0) + levels - 1) {
+    case 0: return launch_cascade_t<double, false, 2, 1, 2, false>(t, st);
+    case 1: return launch_cascade_t<double, false, 2, 2, 1, false>(t, st);
+    case 2: return launch_cascade_t<double, false, 2, 1, 2, true>(t, st);
+    case 4: return launch_cascade_t<float, false, 2, 1, 4, false>(t, st);
+    case 5: return launch_cascade_t<float, false, 2, 2, 3, false>(t, st);
+    case 6: return launch_cascade_t<float, false, 2, 1, 4, true>(t, st);
+    case 8: return launch_cascade_t<float, true, 2, 1, 4, false>(t, st);
+    case 9: return launch_cascade_t<float, true, 2, 2, 3, false>(t, st);
+    case 10: return launch_cascade_t<float, true, 2, 1, 4, true>(t, st);
+    case 12: return launch_cascade_t<_Float16, true, 4, 1, 3, false>(t, st);
+    case 14: return launch_cascade_t<_Float16, true, 4, 1, 3, true>(t, st);
     }
     return hipErrorInvalidValue;
 }

@@ -51,14 +51,14 @@ using SlotArena = lbm::Arena<DeviceAlloc>;
 struct GraphEntry {
     // single- or two-step launches, then cascade passes
     int nfirst = 0, nitems = 0, vx = 0, nw = 0, nts = 0, ch = 0, two = 0;
-    int deep_vx = 0, deep_passes = 0, deep_items = 0, deep_lats_at = 0;
+    int deep_passes = 0, deep_items = 0, deep_lats_at = 0;
     const BatchLat* lats = nullptr;
     const int* items = nullptr;
     hipGraphExec_t exec = nullptr;
     bool same(const GraphEntry& o) const
     {
         return nfirst == o.nfirst && nitems == o.nitems && vx == o.vx && nw == o.nw && nts == o.nts && ch == o.ch &&
-               two == o.two && deep_vx == o.deep_vx && deep_passes == o.deep_passes && deep_items == o.deep_items &&
+               two == o.two && deep_passes == o.deep_passes && deep_items == o.deep_items &&
                deep_lats_at == o.deep_lats_at && lats == o.lats && items == o.items;
     }
 };
@@ -127,7 +127,7 @@ struct lbm_pool {
     std::vector<GraphEntry> graphs;
     // Cascade passes of the call being built: their descriptors and items
     // follow the others' in h_lats and h_items.
-    int deep_vx = 0, deep_passes = 0, deep_lats_at = 0, deep_items_at = 0;
+    int deep_passes = 0, deep_lats_at = 0, deep_items_at = 0;
     std::vector<int> sizes;
 };
 
@@ -159,7 +159,7 @@ void advance(Slot& S, int n, int two)
 // cascade passes of four steps.
 void advance_deep(Slot& S, int n)
 {
-    S.ph = (int)((S.ph + (n % kCascadeSteps + 1) / 2 + n / kCascadeSteps + n) & 1);
+    S.ph = (int)((S.ph + (n % kCascadeWaves + 1) / 2 + n / kCascadeWaves + n) & 1);
     S.t += n;
 }
 
@@ -291,7 +291,7 @@ hipError_t run_batch(lbm_pool* P, int nmax)
     const int nlaunch = nfirst + P->deep_passes;
     auto launch_k = [&](int k) {
         if (k >= nfirst)
-            return launch_batch_cascade(P->dtype, P->deep_vx, P->d_lats + P->deep_lats_at, P->d_items + nitems,
+            return launch_batch_cascade(P->dtype, P->d_lats + P->deep_lats_at, P->d_items + nitems,
                                         deep_items, k - nfirst, P->stream);
         return P->two ? launch_batch2(P->dtype, P->vx, P->nw, nts, P->d_lats, P->d_items, nitems, k, P->xcd_chunk,
                                       P->stream)
@@ -307,7 +307,6 @@ hipError_t run_batch(lbm_pool* P, int nmax)
         key.nts = P->nts;
         key.ch = P->xcd_chunk;
         key.two = P->two;
-        key.deep_vx = P->deep_vx;
         key.deep_passes = P->deep_passes;
         key.deep_items = deep_items;
         key.deep_lats_at = P->deep_lats_at;
@@ -354,7 +353,7 @@ CascadeShape pool_cascade(lbm_pool* P, const int* slots, const int* nsteps, int 
     for (int d = 0; d < 2; ++d)
         for (int k = 0; k < count; ++k) {
             const Slot& S = P->slots[slots[k]];
-            if (nsteps[k] < kCascadeSteps) continue;
+            if (nsteps[k] < kCascadeWaves) continue;
             if (S.g.rs != 9LL * S.g.pitch) return {};  // plane-major: past 32-bit offsets
             P->sizes.push_back(d == 0 ? S.nx : S.ny);
         }
@@ -369,7 +368,7 @@ void add_cascade(lbm_pool* P, const Slot& S, const CascadeShape& c, int passes, 
 {
     BatchLat b{};
     b.tile = slot_tile(S, P->vx, P->nw, P->two);
-    const int w = cascade_cols(c.vx, kCascadeSteps, P->esize);
+    const int w = cascade_cols(cascade_vx(P->dtype), kCascadeWaves, P->esize);
     // chunks of even height, a whole number of the kernel's turns of four rows
     const int chunks = (S.ny + c.h - 1) / c.h;
     b.tile.h = ((S.ny + chunks - 1) / chunks + 1) / 4 * 4 + 2;
@@ -559,7 +558,7 @@ static int build_batch(lbm_pool* P, const int* slots, const int* nsteps, int cou
     if (!P || count < 0 || (count > 0 && (!slots || !nsteps))) return LBM_EINVAL;
     P->h_lats.clear();
     P->h_items.clear();
-    P->deep_vx = P->deep_passes = 0;
+    P->deep_passes = 0;
     *nmax = 0;
     *took = false;
     for (int k = 0; k < count; ++k) {
@@ -571,7 +570,7 @@ static int build_batch(lbm_pool* P, const int* slots, const int* nsteps, int cou
     }
     const CascadeShape c = deep ? pool_cascade(P, slots, nsteps, count) : CascadeShape{};
     for (int k = 0; k < count; ++k) {
-        const int n = c.vx ? nsteps[k] % kCascadeSteps : nsteps[k];
+        const int n = c.levels ? nsteps[k] % kCascadeWaves : nsteps[k];
         if (n == 0) continue;
         const Slot& S = P->slots[slots[k]];
         BatchLat b{};
@@ -583,14 +582,13 @@ static int build_batch(lbm_pool* P, const int* slots, const int* nsteps, int cou
     }
     P->deep_lats_at = (int)P->h_lats.size();
     P->deep_items_at = (int)P->h_items.size();
-    if (c.vx) {
+    if (c.levels) {
         *took = true;
-        P->deep_vx = c.vx;
         for (int k = 0; k < count; ++k) {
-            if (nsteps[k] < kCascadeSteps) continue;
+            if (nsteps[k] < kCascadeWaves) continue;
             const Slot& S = P->slots[slots[k]];
-            const int left = nsteps[k] % kCascadeSteps;
-            add_cascade(P, S, c, nsteps[k] / kCascadeSteps, buffer_time(S) + (left + 1) / 2);
+            const int left = nsteps[k] % kCascadeWaves;
+            add_cascade(P, S, c, nsteps[k] / kCascadeWaves, buffer_time(S) + (left + 1) / 2);
         }
     }
     return LBM_OK;
@@ -820,7 +818,7 @@ int lbm_pool_autotune(lbm_pool* P, const int* slots, int count, int reps, int us
         P->nw = d.nw;
         P->nts = d.nts;
         P->two = d.two;
-        const std::vector<int> steps(count, kCascadeSteps);
+        const std::vector<int> steps(count, kCascadeWaves);
         four = pool_cascade(P, slots, steps.data(), count);
         P->vx = now.vx;
         P->nw = now.nw;
@@ -833,7 +831,7 @@ int lbm_pool_autotune(lbm_pool* P, const int* slots, int count, int reps, int us
         const bool nts = (k.flags & LBM_TILE_NT_STORE) != 0;
         const CascadeShape deep = is_deep_tile(P->dtype, k.vx, k.nw, nts, two) ? four : CascadeShape{};
         auto go = [&]() {
-            if (deep.vx) return launch_batch_cascade(P->dtype, deep.vx, P->d_lats, P->d_items, nitems, 0, P->stream);
+            if (deep.levels) return launch_batch_cascade(P->dtype, P->d_lats, P->d_items, nitems, 0, P->stream);
             hipError_t ge = hipSuccess;
             for (int r = 0; r < (two ? 2 : 4) && ge == hipSuccess; ++r) {
                 if (two && pers)
@@ -859,7 +857,7 @@ int lbm_pool_autotune(lbm_pool* P, const int* slots, int count, int reps, int us
         P->h_items.clear();
         P->deep_lats_at = P->deep_items_at = 0;
         for (int j = 0; j < count; ++j) {
-            if (deep.vx) {
+            if (deep.levels) {
                 add_cascade(P, P->slots[slots[j]], deep, 1, buffer_time(P->slots[slots[j]]));
                 continue;
             }

@@ -31,7 +31,7 @@ struct lbm_lattice {
     bool ready;
     int vx, nw, h;     // step tile
     int kflags;        // LBM_TILE_* bits
-    CascadeShape deep; // cascade passes of the default shape (see next_pass)
+    CascadeShape deep[2]; // cascade passes of the default shape, of four and eight steps (see next_pass)
     void* field;       // per-site source coefficients of a c2 field, or nullptr
     int fpitch;        // its row pitch (elements)
     int xbc;           // lbm_xbc
@@ -150,8 +150,9 @@ Pass next_pass(const lbm_lattice* L, int n)
             const BlockShape b = block_shape(L->dtype, L->nx, L->ny, n, inlet);
             if (b.ns) return {Pass::kBlock, b.ns, b};
         }
-        if (!inlet && L->deep.vx && n >= kCascadeSteps && L->g.rs == 9LL * L->g.pitch)
-            return {Pass::kCascade, kCascadeSteps, {}};
+        if (!inlet && L->g.rs == 9LL * L->g.pitch)
+            for (int k = L->field ? 0 : 1; k >= 0; --k)
+                if (L->deep[k].levels && n >= kCascadeWaves * (k + 1)) return {Pass::kCascade, kCascadeWaves * (k + 1), {}};
     }
     if ((L->kflags & LBM_TILE_TWO_STEP) && !inlet && n >= 2) return {Pass::kPair, 2, {}};
     return {Pass::kStep, 1, {}};
@@ -170,12 +171,13 @@ hipError_t launch_pass(const lbm_lattice* L, const Pass& p, bool last)
         return launch_block(L->dtype, p.block, t, L->xbc == LBM_XBC_INLET_OUTLET ? &in : nullptr, L->stream);
     }
     case Pass::kCascade: {
-        const int w = cascade_cols(L->deep.vx, kCascadeSteps, L->esize);
-        t.h = L->deep.h;
+        const CascadeShape& c = L->deep[p.steps / kCascadeWaves - 1];
+        const int w = cascade_cols(cascade_vx(L->dtype), p.steps, L->esize);
+        t.h = c.h;
         t.nstrips = (L->nx + w - 1) / w;
         t.nchunks = (L->ny + t.h - 1) / t.h;
         t.xcd_chunk = 0;  // one run of chunks per XCD: neighbouring strips share their halo's lines in its L2
-        hipError_t e = launch_cascade(L->dtype, L->deep.vx, t, L->stream);
+        hipError_t e = launch_cascade(L->dtype, c.levels, t, L->stream);
         if (e == hipSuccess && last) e = launch_ghosts(L->dtype, L->nxt, L->g, L->stream);
         return e;
     }
@@ -285,7 +287,7 @@ lbm_lattice* lbm_create(int nx, int ny, double tau, double c2, int dtype)
     L->h = td.h;
     L->kflags = td.flags;
     apply_tile_env(dtype, &L->vx, &L->nw, &L->h, &L->kflags);
-    L->deep = lbm::cascade_shape(dtype, nx, ny);
+    lbm::cascade_shapes(dtype, nx, ny, L->deep);
     hipError_t e = hipGetDevice(&L->device);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&L->own, hipStreamNonBlocking);
     if (e != hipSuccess) {
@@ -380,7 +382,7 @@ int lbm_autotune(lbm_lattice* L, int reps, int use_cache)
         cands.erase(std::remove_if(cands.begin(), cands.end(),
                                    [](const TileCand& k) { return !(k.flags & LBM_TILE_VSTACK); }),
                     cands.end());
-    // Each candidate is timed over four steps, as lbm_step would launch them
+    // Each candidate is timed over eight steps, as lbm_step would launch them
     // (the inlet aside), reading cur and writing nxt with no swap: the state
     // does not change.
     auto launch = [&](const TileCand& k) -> hipError_t {
@@ -391,7 +393,7 @@ int lbm_autotune(lbm_lattice* L, int reps, int use_cache)
         tmp.kflags = k.flags;
         tmp.xbc = LBM_XBC_PERIODIC;
         hipError_t e = hipSuccess;
-        for (int n = 4; n > 0 && e == hipSuccess;) {
+        for (int n = 8; n > 0 && e == hipSuccess;) {
             const Pass p = next_pass(&tmp, n);
             e = launch_pass(&tmp, p, true);
             n -= p.steps;

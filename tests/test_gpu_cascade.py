@@ -1,7 +1,7 @@
-"""The cascade kernel (four steps of Eq. 5 per pass, rows falling through four
-levels held in registers), which the default shape takes on large lattices,
-gives the bits of single steps: strips one column short of, at and past a
-strip's width (48 or 112 columns), lattices narrower than a strip (whose lanes
+"""The cascade kernel (four or eight steps of Eq. 5 per pass, rows falling
+through the levels that four waves hold in registers), which the default shape
+takes on large lattices, gives the bits of single steps: strips one column
+short of, at and past a strip's width (112 or 240 columns, 96 with eight steps), lattices narrower than a strip (whose lanes
 wrap several times), lower than a pass's halo (whose rows wrap several times)
 and with ragged last chunks; every stored type, the altered-equilibrium model,
 c2 fields; step counts with every remainder of four."""
@@ -50,6 +50,17 @@ def test_cascade_bitwise_equals_single_steps(dtype, nx, ny):
     f = fields(nx, ny, nx + ny)
     for calls in ((8,), (4, 5), (7, 6)):
         ref = run(nx, ny, dtype, (sum(calls),), f, SINGLE)
+        got = run(nx, ny, dtype, calls, f)
+        assert np.array_equal(got, ref), (dtype, nx, ny, calls)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32", "f32s", "f16s"])
+@pytest.mark.parametrize("nx,ny", [(95, 52009), (96, 52003), (97, 52001), (193, 30011), (239, 30011), (241, 30013),
+                                   (260003, 19), (4003, 1501)])
+def test_cascade_eight_steps_and_remainders_bitwise(dtype, nx, ny):
+    f = fields(nx, ny, nx + ny)
+    ref = run(nx, ny, dtype, (29,), f, SINGLE)
+    for calls in ((29,), (8, 12, 9)):  # 3 passes of eight, one of four, a single step
         got = run(nx, ny, dtype, calls, f)
         assert np.array_equal(got, ref), (dtype, nx, ny, calls)
 
