@@ -214,14 +214,14 @@ size_t lbm_footprint_bytes(int nx, int ny, int dtype);
  * LBM_F32, LBM_F32S or LBM_F16S); a workgroup writes nw - 6 rows and
  * (64 - 2 ceil(3 / vx)) vx columns. lbm_step takes the steps in pairs; a lone last step, and every
  * step while inlet/outlet boundaries are set, use the single-step vertical
- * stack (vx = 2, nw = 8, non-temporal stores). The
+ * stack (vx = 2, nw = 8, non-temporal stores), the passes below aside. The
  * results are those of single steps, bit for bit (c2 fields included).
- * With the dtype's default shape, lattices large enough (from about 700^2
- * sites) that fit the row-interleaved layout advance four steps per launch
- * instead (the cascade kernel); the pairs take what is left of a count.
+ * With the dtype's default shape, lattices large enough (from about 600^2
+ * sites) that fit the row-interleaved layout advance four or eight steps per
+ * launch instead (the cascade kernel); the pairs take what is left of a count.
  * Small lattices (at most 16 rows, or up to about 250^2 sites) advance up to
- * 15 or 4 steps per launch (the block kernel), inlet/outlet boundaries
- * included.
+ * 15 or 4 steps per launch (the block kernel). Both take inlet/outlet
+ * boundaries, except together with a c2 field.
  * lbm_get_tile: any pointer may be NULL. */
 enum lbm_tile_flags {
     LBM_TILE_PREFETCH = 1, /* issue the next row's loads before relaxing the current row */

@@ -24,11 +24,4 @@ struct BlockShape {
 // inlet: with inlet/outlet boundaries.
 BlockShape block_shape(int dtype, int nx, int ny, int n, bool inlet);
 
-// Inlet/outlet boundaries during a block pass that starts at time t.
-struct BlockInlet {
-    double amplitude, period;
-    long long t;
-    double eqs;  // the model's equilibrium shift
-};
-
 }  // namespace lbm

@@ -23,6 +23,7 @@
 #include "host.h"
 #include "internal.h"
 #include "step.h"
+#include "xbc.h"
 
 namespace lbm {
 
@@ -32,20 +33,13 @@ template <class C> struct BlockLds {
     C f[6][kBlockWaves][LW];  // planes 2, 5, 6 (e_iy = 1), 4, 7, 8 (e_iy = -1)
 };
 
-// Inlet/outlet boundaries (Fig. 1) during a pass: the stored rest equilibria
-// of the rest, axis and diagonal links at the inlet density of each step,
-// and at density 1.
-template <class T> struct BlockXbc {
-    T in[kBlockMaxSteps][3];
-    T one[3];
-};
 struct BlockPeriodic {};
 
 // XBC: the sites of columns 0 and nx - 1 emit the values of xb in place of
 // their results (as launch_xbc writes them after a single step).
 template <class T, bool SHIFT, bool FIELD, bool XBC>
 __global__ __launch_bounds__(64 * kBlockWaves) void block_kernel(
-    StepTile a, int ns, int halo, typename std::conditional<XBC, BlockXbc<T>, BlockPeriodic>::type xb)
+    StepTile a, int ns, int halo, typename std::conditional<XBC, XbcValues<T>, BlockPeriodic>::type xb)
 {
     using C = typename CompT<T>::type;
     constexpr bool RC = ModelCentred<C>::value;
@@ -107,11 +101,7 @@ __global__ __launch_bounds__(64 * kBlockWaves) void block_kernel(
         for (int i = 0; i < 9; ++i) f[i] = from_d<T, SHIFT, C>(o[i], i, cn);
         if constexpr (XBC) {
 #pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                const int cls = i == 0 ? 0 : (i < 5 ? 1 : 2);
-                const T in = xb.in[s][cls], one = xb.one[cls];
-                f[i] = xw == 0 ? (ex[i] < 0 ? one : in) : (xw == g.nx - 1 ? (ex[i] > 0 ? in : one) : f[i]);
-            }
+            for (int i = 0; i < 9; ++i) f[i] = xbc_value<T>(xb, s, i, ex[i], xw, g.nx, f[i]);
         }
         if (s == ns - 1) break;
         C q[9];
@@ -140,29 +130,14 @@ __global__ __launch_bounds__(64 * kBlockWaves) void block_kernel(
     }
 }
 
-// The stored rest equilibrium of link class c (rest, axis, diagonal) at
-// density rho, with the operations of xbc_kernel.
-template <class T, bool SHIFT> static T rest_value(int c, double rho, double eqs)
-{
-    const double w0 = 4.0 / 9.0, w = c == 0 ? w0 : (c == 1 ? 1.0 / 9.0 : 1.0 / 36.0);
-    const double r = SHIFT ? rho - 1.0 : rho;
-    return (T)(w * r + (c == 0 ? -(1.0 - w0) * r * eqs : w * r * eqs));
-}
-
 template <class T, bool SHIFT>
-static hipError_t launch_block_t(const BlockShape& b, const StepTile& t, const BlockInlet* inlet, hipStream_t st)
+static hipError_t launch_block_t(const BlockShape& b, const StepTile& t, const PassInlet* inlet, hipStream_t st)
 {
     const dim3 grid((unsigned)(t.nstrips * t.nchunks)), block(64 * b.waves);
     const int halo = b.halo(t.g.ny);
     if (!grid_fits((long long)grid.x, (int)block.x)) return hipErrorInvalidConfiguration;
     if (inlet) {
-        BlockXbc<T> xb;
-        for (int c = 0; c < 3; ++c) {
-            xb.one[c] = rest_value<T, SHIFT>(c, 1.0, inlet->eqs);
-            for (int s = 0; s < kBlockMaxSteps; ++s)
-                xb.in[s][c] = rest_value<T, SHIFT>(
-                    c, inlet_density(inlet->amplitude, inlet->period, inlet->t + (s < b.ns ? s : 0)), inlet->eqs);
-        }
+        const XbcValues<T> xb = xbc_values<T, SHIFT>(*inlet, b.ns);
         hipLaunchKernelGGL((block_kernel<T, SHIFT, false, true>), grid, block, 0, st, t, b.ns, halo, xb);
     } else if (t.field) {
         hipLaunchKernelGGL((block_kernel<T, SHIFT, true, false>), grid, block, 0, st, t, b.ns, halo, BlockPeriodic{});
@@ -174,7 +149,7 @@ static hipError_t launch_block_t(const BlockShape& b, const StepTile& t, const B
 
 // b.ns steps; t's strips and groups are those of b. inlet: the boundaries in
 // x, or nullptr (periodic).
-hipError_t launch_block(int dtype, const BlockShape& b, const StepTile& t, const BlockInlet* inlet, hipStream_t st)
+hipError_t launch_block(int dtype, const BlockShape& b, const StepTile& t, const PassInlet* inlet, hipStream_t st)
 {
     if (b.ns < 1 || b.ns > kBlockMaxSteps || b.waves < 1 || b.waves > kBlockWaves || b.rows(t.g.ny) < 1)
         return hipErrorInvalidValue;
@@ -200,8 +175,10 @@ hipError_t launch_block(int dtype, const BlockShape& b, const StepTile& t, const
 // FP64 2.82 and 1.83; 256^2 FP32 215 tiles 3.62 and 2.63, 320^2 324 tiles
 // 3.65 and 3.49), in FP64, whose LDS traffic is twice as much, 3 steps up to
 // half of that (192^2 128 tiles 2.91 and 2.85; 220^2 185 tiles 2.98 and
-// 3.25). With inlet/outlet boundaries the alternative is two launches per
-// step: 3 steps up to 2500 tiles (1000 x 777, FP32, 10.2 us per step).
+// 3.25). With inlet/outlet boundaries the alternative is a cascade pass: 3
+// steps up to 800 tiles in FP64 (400^2 5.5 us per step, cascade 6.3; 512^2 7.3
+// and 7.1), 1250 in FP32 (600^2 5.6 and 5.8; 700^2 7.0 and 5.8), 2500 in FP16
+// (1000 x 777 10.5 and 12.3).
 BlockShape block_shape(int dtype, int nx, int ny, int n, bool inlet)
 {
     BlockShape best;
@@ -232,7 +209,8 @@ BlockShape block_shape(int dtype, int nx, int ny, int n, bool inlet)
     b.ns = 4;
     if (b.tiles(nx, ny) > 256) {
         b.ns = 3;
-        if (b.tiles(nx, ny) > (inlet ? 2500 : (dtype == 0 ? 128 : 256))) return best;
+        static const int most[4] = {800, 1250, 1250, 2500};
+        if (b.tiles(nx, ny) > (inlet ? most[dtype] : (dtype == 0 ? 128 : 256))) return best;
     }
     if (b.ns > n) b.ns = n;
     return b;

@@ -38,8 +38,8 @@ constexpr int cascade_vx(int dtype) { return dtype == 3 ? 4 : 2; }
 struct CascadeShape {
     int levels = 0, h = 0;
 };
-// out[0]: four steps per pass, out[1]: eight.
-void cascade_shapes(int dtype, int nx, int ny, CascadeShape out[2]);
+// out[0]: four steps per pass, out[1]: eight. inlet: with inlet/outlet boundaries.
+void cascade_shapes(int dtype, int nx, int ny, bool inlet, CascadeShape out[2]);
 // Four steps per pass of a batch of lattices of the given sizes (nx[k] x ny[k]).
 CascadeShape cascade_batch_shape(int dtype, const int* nx, const int* ny, int count);
 

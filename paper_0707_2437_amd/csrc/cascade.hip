@@ -38,6 +38,7 @@
 #include "host.h"
 #include "internal.h"
 #include "step.h"
+#include "xbc.h"
 
 namespace lbm {
 
@@ -47,6 +48,7 @@ template <class T, bool SHIFT, int VX> struct CascadeRow {
     using C = typename CompT<T>::type;
     using Mem = Pack<T, VX>;  // as loaded and stored
     static __device__ __forceinline__ T get(const Mem& p, int j) { return p.v[j]; }
+    template <int J> static __device__ __forceinline__ void put(Mem& p, T v) { p.v[J] = v; }
     template <class F> static __device__ __forceinline__ Mem each(F&& f)  // column j: f(j)
     {
         Mem p;
@@ -103,9 +105,14 @@ template <int VX> struct CascadeRow<_Float16, true, VX> {
     struct Mem {
         unsigned q[Q];
     };
-    static __device__ __forceinline__ unsigned short get(const Mem& p, int j)
+    static __device__ __forceinline__ _Float16 get(const Mem& p, int j)
     {
-        return (unsigned short)(p.q[j >> 1] >> (16 * (j & 1)));
+        return __builtin_bit_cast(_Float16, (unsigned short)(p.q[j >> 1] >> (16 * (j & 1))));
+    }
+    template <int J> static __device__ __forceinline__ void put(Mem& p, _Float16 v)
+    {
+        const unsigned h = (unsigned)__builtin_bit_cast(unsigned short, v);
+        p.q[J / 2] = J & 1 ? (p.q[J / 2] & 0xffffu) | h << 16 : (p.q[J / 2] & 0xffff0000u) | h;
     }
     template <class F> static __device__ __forceinline__ Mem each(F&& f)
     {
@@ -164,6 +171,9 @@ template <int VX> struct CascadeRow<_Float16, true, VX> {
 // densities w), the densities of the row above it (wp), and the planes of
 // its last results that wait for rows below: e_iy = 0 of the last row (z),
 // e_iy = 1 of the last two (up, by the row's parity).
+// Stands for XbcValues where the lattice is periodic in x.
+struct CascadePeriodic {};
+
 template <class R> struct CascadeWait {
     R z[3], up[2][3];
 };
@@ -198,15 +208,17 @@ __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t rs, const V v, 
 // inner columns. EDGE: a strip whose window reaches past the lattice's left
 // or right edge; its lanes load every element from its wrapped column
 // (Sec. 4: periodic in x) and store element by element.
-template <class T, bool SHIFT, int VX, int NL, bool FIRST, bool LAST, bool FIELD, bool RC, bool EDGE>
+template <class T, bool SHIFT, int VX, int NL, bool FIRST, bool LAST, bool FIELD, bool RC, bool EDGE, class XB>
 __device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src, void* dst, int strip, int chunk,
                                              [[maybe_unused]] typename CascadeRow<T, SHIFT, VX>::Mem (*in)[9][64],
                                              [[maybe_unused]] typename CascadeRow<T, SHIFT, VX>::Mem (*outq)[9][64],
-                                             int w)
+                                             int w, [[maybe_unused]] const XB& xb)
 {
     using C = typename CompT<T>::type;
     using R = CascadeRow<T, SHIFT, VX>;
     using Mem = typename R::Mem;
+    // only a strip whose window reaches past an edge holds columns 0 and nx - 1
+    constexpr bool XBC = EDGE && !std::is_same<XB, CascadePeriodic>::value;
     constexpr int NW = kCascadeWaves, NS = NL * NW;
     constexpr unsigned es = sizeof(T);
     constexpr int H = cascade_halo(NS), HL = cascade_halo_lanes(VX, NS, es), W = cascade_cols(VX, NS, es);
@@ -417,6 +429,16 @@ __device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src,
                 // columns, and levels, one after the other: interleaved they need more registers
                 __builtin_amdgcn_sched_barrier(0);
             });
+            if constexpr (XBC) {
+                static_for<0, VX>([&](auto jc) {
+                    constexpr int j = decltype(jc)::value;
+                    const int xw = (int)(off[j + 1] / es) - 2;
+                    static_for<0, 9>([&](auto ic) {
+                        constexpr int i = decltype(ic)::value;
+                        R::template put<j>(f[i], xbc_value<T>(xb, w * NL + s, i, ex[i], xw, g.nx, R::get(f[i], j)));
+                    });
+                });
+            }
 #pragma unroll
             for (int j = 0; j < VX; ++j) {
                 l.wp[j] = l.w[j];
@@ -476,24 +498,25 @@ template <class T, bool SHIFT, int VX> struct CascadeRing {
 
 // One wave of a team. The waves pass the same number of barriers: a wave's
 // first row is one barrier behind that of the wave before it.
-template <class T, bool SHIFT, int VX, int NL, bool FIELD, bool RC, bool EDGE>
+template <class T, bool SHIFT, int VX, int NL, bool FIELD, bool RC, bool EDGE, class XB>
 __device__ __forceinline__ void cascade_wave(const StepTile& a, const void* src, void* dst, int strip, int chunk,
-                                             CascadeRing<T, SHIFT, VX>& ring)
+                                             CascadeRing<T, SHIFT, VX>& ring, const XB& xb)
 {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (w == 0)
-        cascade_tile<T, SHIFT, VX, NL, true, false, FIELD, RC, EDGE>(a, src, dst, strip, chunk, nullptr, ring.row[0], 0);
+        cascade_tile<T, SHIFT, VX, NL, true, false, FIELD, RC, EDGE>(a, src, dst, strip, chunk, nullptr, ring.row[0], 0, xb);
     else if (w == kCascadeWaves - 1)
-        cascade_tile<T, SHIFT, VX, NL, false, true, FIELD, RC, EDGE>(a, src, dst, strip, chunk, ring.row[w - 1], nullptr, w);
+        cascade_tile<T, SHIFT, VX, NL, false, true, FIELD, RC, EDGE>(a, src, dst, strip, chunk, ring.row[w - 1], nullptr, w,
+                                                                    xb);
     else
         cascade_tile<T, SHIFT, VX, NL, false, false, FIELD, RC, EDGE>(a, src, dst, strip, chunk, ring.row[w - 1],
-                                                                      ring.row[w], w);
+                                                                      ring.row[w], w, xb);
 }
 
 // MW: waves per SIMD the registers are held to.
-template <class T, bool SHIFT, int VX, int NL, int MW, bool FIELD>
+template <class T, bool SHIFT, int VX, int NL, int MW, bool FIELD, class XB>
 __global__ __launch_bounds__(64 * kCascadeWaves) __attribute__((amdgpu_waves_per_eu(MW, MW))) void cascade_kernel(
-    StepTile a, int ntiles)
+    StepTile a, int ntiles, XB xb)
 {
     constexpr bool RC = ModelCentred<typename CompT<T>::type>::value;
     constexpr int es = sizeof(T), NS = NL * kCascadeWaves, W = cascade_cols(VX, NS, es),
@@ -504,9 +527,9 @@ __global__ __launch_bounds__(64 * kCascadeWaves) __attribute__((amdgpu_waves_per
     const int strip = t % a.nstrips, chunk = t / a.nstrips;
     const int x0 = strip * W - HL * VX;  // the strip's window
     if (x0 - 1 < 0 || x0 + 64 * VX + 1 > a.g.nx)
-        cascade_wave<T, SHIFT, VX, NL, FIELD, RC, true>(a, a.src, a.dst, strip, chunk, ring);
+        cascade_wave<T, SHIFT, VX, NL, FIELD, RC, true>(a, a.src, a.dst, strip, chunk, ring, xb);
     else
-        cascade_wave<T, SHIFT, VX, NL, FIELD, RC, false>(a, a.src, a.dst, strip, chunk, ring);
+        cascade_wave<T, SHIFT, VX, NL, FIELD, RC, false>(a, a.src, a.dst, strip, chunk, ring, xb);
 }
 
 // Batched form: pass p of every lattice of a batch (BatchLat in internal.h,
@@ -533,9 +556,9 @@ __global__ __launch_bounds__(64 * kCascadeWaves) __attribute__((amdgpu_waves_per
     const int strip = t % L.tile.nstrips, chunk = t / L.tile.nstrips;
     const int x0 = strip * W - HL * VX;
     if (x0 - 1 < 0 || x0 + 64 * VX + 1 > L.tile.g.nx)
-        cascade_wave<T, SHIFT, VX, NL, false, RC, true>(L.tile, src, dst, strip, chunk, ring);
+        cascade_wave<T, SHIFT, VX, NL, false, RC, true>(L.tile, src, dst, strip, chunk, ring, CascadePeriodic{});
     else
-        cascade_wave<T, SHIFT, VX, NL, false, RC, false>(L.tile, src, dst, strip, chunk, ring);
+        cascade_wave<T, SHIFT, VX, NL, false, RC, false>(L.tile, src, dst, strip, chunk, ring, CascadePeriodic{});
 }
 
 // The time a team takes per row on MI355X, in us, with one, two ... teams on
@@ -575,14 +598,17 @@ static double cascade_bytes_per_us(double state_bytes) { return state_bytes > 2.
 // 4.8, 700^2 6.5 and 5.4, 1000 x 777 8.9 and 6.5; FP64 512^2 6.2 and 6.3, 700^2
 // 10.5 and 8.0. Four-step against eight-step: FP32 1000 x 777 6.5 and 7.6,
 // 2048^2 21.4 and 19.3, 4096^2 70.0 and 59.6; FP64 1000 x 777 10.5 and 10.8,
-// 2048^2 34.6 and 35.9, 4096^2 123.8 and 111.6.
-void cascade_shapes(int dtype, int nx, int ny, CascadeShape out[2])
+// 2048^2 34.6 and 35.9, 4096^2 123.8 and 111.6. With an inlet, single steps and
+// a boundary launch after each against passes: FP32 700^2 13.3 and 5.8, 4096^2
+// 209.7 and 64.6; FP64 4096^2 422 and 120; FP16 1400^2 23.5 and 15.1.
+void cascade_shapes(int dtype, int nx, int ny, bool inlet, CascadeShape out[2])
 {
     static const double two_step[4][2] = {{2.4, 14.9}, {2.6, 7.4}, {2.6, 7.4}, {2.8, 4.7}};
     const int es = dtype == 0 ? 8 : (dtype == 3 ? 2 : 4);
     const double sites = (double)nx * ny, per_us = cascade_bytes_per_us(sites * 18 * es);
-    // us per step of the best so far
-    double t_best = two_step[dtype][0] + two_step[dtype][1] * sites * 1e-6;
+    // us per step of the best so far; with an inlet, single steps and a launch
+    // for the boundary after each
+    double t_best = inlet ? 4.5 + 2.3 * es * sites * 1e-6 : two_step[dtype][0] + two_step[dtype][1] * sites * 1e-6;
     for (int levels = 1; levels <= 2; ++levels) {
         out[levels - 1] = CascadeShape();
         const int ns = levels * kCascadeWaves, warm = 2 * cascade_halo(ns);
@@ -659,32 +685,41 @@ hipError_t launch_batch_cascade(int dtype, const BatchLat* lats, const int* item
 }
 
 template <class T, bool SHIFT, int VX, int NL, int MW, bool FIELD>
-static hipError_t launch_cascade_t(const StepTile& t, hipStream_t st)
+static hipError_t launch_cascade_t(const StepTile& t, const PassInlet* inlet, hipStream_t st)
 {
     const int ntiles = t.nstrips * t.nchunks, threads = 64 * kCascadeWaves;
     const int q = t.xcd_chunk > 0 ? 8 * t.xcd_chunk : 8;
     const int grid = (ntiles + q - 1) / q * q;
     if (!grid_fits(grid, threads)) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((cascade_kernel<T, SHIFT, VX, NL, MW, FIELD>), dim3(grid), dim3(threads), 0, st, t, ntiles);
+    if (!inlet) {
+        hipLaunchKernelGGL((cascade_kernel<T, SHIFT, VX, NL, MW, FIELD, CascadePeriodic>), dim3(grid), dim3(threads), 0,
+                           st, t, ntiles, CascadePeriodic{});
+    } else {
+        if constexpr (FIELD) return hipErrorInvalidValue;
+        else
+            hipLaunchKernelGGL((cascade_kernel<T, SHIFT, VX, NL, MW, false, XbcValues<T>>), dim3(grid), dim3(threads), 0,
+                               st, t, ntiles, xbc_values<T, SHIFT>(*inlet, NL * kCascadeWaves));
+    }
     return hipGetLastError();
 }
 
 // levels: per wave; 2 (eight steps per pass) without a c2 field, whose rows
-// would take the registers past their limit, and not for FP16.
-hipError_t launch_cascade(int dtype, int levels, const StepTile& t, hipStream_t st)
+// would take the registers past their limit, and not for FP16. inlet: the
+// boundaries in x, or null (periodic); not with a c2 field.
+hipError_t launch_cascade(int dtype, int levels, const StepTile& t, const PassInlet* in, hipStream_t st)
 {
     switch (dtype * 4 + (t.field ? 2 : 0) + levels - 1) {
-    case 0: return launch_cascade_t<double, false, 2, 1, 2, false>(t, st);
-    case 1: return launch_cascade_t<double, false, 2, 2, 1, false>(t, st);
-    case 2: return launch_cascade_t<double, false, 2, 1, 2, true>(t, st);
-    case 4: return launch_cascade_t<float, false, 2, 1, 4, false>(t, st);
-    case 5: return launch_cascade_t<float, false, 2, 2, 3, false>(t, st);
-    case 6: return launch_cascade_t<float, false, 2, 1, 4, true>(t, st);
-    case 8: return launch_cascade_t<float, true, 2, 1, 4, false>(t, st);
-    case 9: return launch_cascade_t<float, true, 2, 2, 3, false>(t, st);
-    case 10: return launch_cascade_t<float, true, 2, 1, 4, true>(t, st);
-    case 12: return launch_cascade_t<_Float16, true, 4, 1, 3, false>(t, st);
-    case 14: return launch_cascade_t<_Float16, true, 4, 1, 3, true>(t, st);
+    case 0: return launch_cascade_t<double, false, 2, 1, 2, false>(t, in, st);
+    case 1: return launch_cascade_t<double, false, 2, 2, 1, false>(t, in, st);
+    case 2: return launch_cascade_t<double, false, 2, 1, 2, true>(t, in, st);
+    case 4: return launch_cascade_t<float, false, 2, 1, 4, false>(t, in, st);
+    case 5: return launch_cascade_t<float, false, 2, 2, 3, false>(t, in, st);
+    case 6: return launch_cascade_t<float, false, 2, 1, 4, true>(t, in, st);
+    case 8: return launch_cascade_t<float, true, 2, 1, 4, false>(t, in, st);
+    case 9: return launch_cascade_t<float, true, 2, 2, 3, false>(t, in, st);
+    case 10: return launch_cascade_t<float, true, 2, 1, 4, true>(t, in, st);
+    case 12: return launch_cascade_t<_Float16, true, 4, 1, 3, false>(t, in, st);
+    case 14: return launch_cascade_t<_Float16, true, 4, 1, 3, true>(t, in, st);
     }
     return hipErrorInvalidValue;
 }

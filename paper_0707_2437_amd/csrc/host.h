@@ -39,12 +39,18 @@ hipError_t launch_batch2_persistent(int dtype, int vx, int nw, bool nts, const B
 // takes one step, one with nsteps <= 2p none.
 hipError_t launch_batch2(int dtype, int vx, int nw, bool nts, const BatchLat* lats, const int* item_lat, int nitems,
                          int p, int ch, hipStream_t st);
+// Inlet/outlet boundaries during a pass of several steps that starts at time t.
+struct PassInlet {
+    double amplitude, period;
+    long long t;
+    double eqs;  // the model's equilibrium shift
+};
 // kCascadeWaves * levels steps per launch (cascade.hip); t's strips and chunks of t.h
 // rows are those of cascade_cols. The caller brings the ghost columns up to
 // date (launch_ghosts) after the last launch of a call.
-hipError_t launch_cascade(int dtype, int levels, const StepTile& t, hipStream_t st);
+hipError_t launch_cascade(int dtype, int levels, const StepTile& t, const PassInlet* inlet, hipStream_t st);
 // b.ns steps per launch on small lattices (block.hip).
-hipError_t launch_block(int dtype, const BlockShape& b, const StepTile& t, const BlockInlet* inlet, hipStream_t st);
+hipError_t launch_block(int dtype, const BlockShape& b, const StepTile& t, const PassInlet* inlet, hipStream_t st);
 // Cascade pass p of a batch (descriptors with the strips and chunks of
 // cascade_cols, nsteps counting passes).
 hipError_t launch_batch_cascade(int dtype, const BatchLat* lats, const int* item_lat, int nitems, int p, hipStream_t st);

@@ -31,7 +31,9 @@ struct lbm_lattice {
     bool ready;
     int vx, nw, h;     // step tile
     int kflags;        // LBM_TILE_* bits
-    CascadeShape deep[2]; // cascade passes of the default shape, of four and eight steps (see next_pass)
+    // cascade passes of the default shape (see next_pass): periodic and with
+    // inlet/outlet boundaries, of four and eight steps
+    CascadeShape deep[2][2];
     void* field;       // per-site source coefficients of a c2 field, or nullptr
     int fpitch;        // its row pitch (elements)
     int xbc;           // lbm_xbc
@@ -134,8 +136,10 @@ StepTile make_tile(const lbm_lattice* L)
 // (small lattices) or cascade passes (large ones, whose buffer is within
 // reach of 32-bit offsets: the row-interleaved layout); a two-step shape
 // takes pairs; a lone last step, and the steps of a lattice with inlet/outlet
-// boundaries that no block pass takes (launch_xbc follows each), the dtype's
-// default single-step shape; any other shape itself.
+// boundaries that no block or cascade pass takes (launch_xbc follows each), the
+// dtype's default single-step shape; any other shape itself. A pass of eight
+// steps costs less per step than one of four where the lattice has a shape for
+// it, so a count takes eights first.
 struct Pass {
     enum Kind { kStep, kPair, kCascade, kBlock } kind;
     int steps;
@@ -150,9 +154,9 @@ Pass next_pass(const lbm_lattice* L, int n)
             const BlockShape b = block_shape(L->dtype, L->nx, L->ny, n, inlet);
             if (b.ns) return {Pass::kBlock, b.ns, b};
         }
-        if (!inlet && L->g.rs == 9LL * L->g.pitch)
+        if (!(inlet && L->field) && L->g.rs == 9LL * L->g.pitch)
             for (int k = L->field ? 0 : 1; k >= 0; --k)
-                if (L->deep[k].levels && n >= kCascadeWaves * (k + 1)) return {Pass::kCascade, kCascadeWaves * (k + 1), {}};
+                if (L->deep[inlet][k].levels && n >= kCascadeWaves * (k + 1)) return {Pass::kCascade, kCascadeWaves * (k + 1), {}};
     }
     if ((L->kflags & LBM_TILE_TWO_STEP) && !inlet && n >= 2) return {Pass::kPair, 2, {}};
     return {Pass::kStep, 1, {}};
@@ -163,21 +167,22 @@ Pass next_pass(const lbm_lattice* L, int n)
 hipError_t launch_pass(const lbm_lattice* L, const Pass& p, bool last)
 {
     StepTile t = make_tile(L);
+    const bool inlet = L->xbc == LBM_XBC_INLET_OUTLET;
+    const PassInlet in{L->amp, L->period, L->t, eq_shift(L->c2, L->model)};
     switch (p.kind) {
     case Pass::kBlock: {
         t.nstrips = (L->nx + p.block.cols() - 1) / p.block.cols();
         t.nchunks = (L->ny + p.block.rows(L->ny) - 1) / p.block.rows(L->ny);
-        const BlockInlet in{L->amp, L->period, L->t, eq_shift(L->c2, L->model)};
-        return launch_block(L->dtype, p.block, t, L->xbc == LBM_XBC_INLET_OUTLET ? &in : nullptr, L->stream);
+        return launch_block(L->dtype, p.block, t, inlet ? &in : nullptr, L->stream);
     }
     case Pass::kCascade: {
-        const CascadeShape& c = L->deep[p.steps / kCascadeWaves - 1];
+        const CascadeShape& c = L->deep[inlet][p.steps / kCascadeWaves - 1];
         const int w = cascade_cols(cascade_vx(L->dtype), p.steps, L->esize);
         t.h = c.h;
         t.nstrips = (L->nx + w - 1) / w;
         t.nchunks = (L->ny + t.h - 1) / t.h;
         t.xcd_chunk = 0;  // one run of chunks per XCD: neighbouring strips share their halo's lines in its L2
-        hipError_t e = launch_cascade(L->dtype, c.levels, t, L->stream);
+        hipError_t e = launch_cascade(L->dtype, c.levels, t, inlet ? &in : nullptr, L->stream);
         if (e == hipSuccess && last) e = launch_ghosts(L->dtype, L->nxt, L->g, L->stream);
         return e;
     }
@@ -194,7 +199,7 @@ hipError_t launch_pass(const lbm_lattice* L, const Pass& p, bool last)
         t = make_tile(&one);
     }
     hipError_t e = launch_step(L->dtype, one.vx, one.nw, one.kflags, t, L->stream);
-    if (e == hipSuccess && L->xbc == LBM_XBC_INLET_OUTLET)
+    if (e == hipSuccess && inlet)
         e = launch_xbc(L->dtype, L->nxt, L->g, inlet_density(L->amp, L->period, L->t), eq_shift(L->c2, L->model),
                        L->stream);
     return e;
@@ -287,7 +292,7 @@ lbm_lattice* lbm_create(int nx, int ny, double tau, double c2, int dtype)
     L->h = td.h;
     L->kflags = td.flags;
     apply_tile_env(dtype, &L->vx, &L->nw, &L->h, &L->kflags);
-    lbm::cascade_shapes(dtype, nx, ny, L->deep);
+    for (int k = 0; k < 2; ++k) lbm::cascade_shapes(dtype, nx, ny, k == 1, L->deep[k]);
     hipError_t e = hipGetDevice(&L->device);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&L->own, hipStreamNonBlocking);
     if (e != hipSuccess) {

@@ -27,12 +27,14 @@ def fields(nx, ny, seed):
     return 1.0 + r(0.01), r(0.02), r(0.02)
 
 
-def run(nx, ny, dtype, calls, f, tile=None, model=None, c2_field=None):
+def run(nx, ny, dtype, calls, f, tile=None, model=None, c2_field=None, inlet=None):
     with lbm.Lattice(nx, ny, 0.7, 0.3, dtype) as L:
         if model is not None:
             L.set_model(model)
         if c2_field is not None:
             L.set_c2_field(c2_field)
+        if inlet:
+            L.set_x_boundaries(lbm.XBC_INLET_OUTLET, *inlet)
         if tile:
             L.set_tile(*tile)
         L.set_stream(torch.cuda.current_stream())
@@ -74,3 +76,14 @@ def test_cascade_models_and_fields_bitwise(dtype, nx, ny):
         ref = run(nx, ny, dtype, (9,), f, SINGLE, **kw)
         got = run(nx, ny, dtype, (9,), f, **kw)
         assert np.array_equal(got, ref), (dtype, nx, ny, list(kw))
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32", "f32s", "f16s"])
+@pytest.mark.parametrize("nx,ny", [(95, 60013), (97, 60013), (113, 60013), (241, 30013), (200003, 21), (2353, 2251)])
+def test_cascade_inlet_bitwise(dtype, nx, ny):
+    f = fields(nx, ny, nx)
+    for kw in ({}, {"model": lbm.MODEL_EQUILIBRIUM}):
+        ref = run(nx, ny, dtype, (3, 26), f, SINGLE, inlet=(0.02, 17.0), **kw)
+        for calls in ((3, 26), (8, 4, 16, 1)):
+            got = run(nx, ny, dtype, calls, f, inlet=(0.02, 17.0), **kw)
+            assert np.array_equal(got, ref), (dtype, nx, ny, calls)
