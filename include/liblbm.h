@@ -264,7 +264,8 @@ enum lbm_pool_mode {
     LBM_POOL_PERSISTENT = 2 /* one launch for all steps of a call: the workgroups
                                resident when it starts take items dynamically, with a
                                grid barrier between steps (between two-step passes in
-                               two-step tiles)                                         */
+                               two-step tiles, between cascade passes of four steps;
+                               then remainders of four are a launch of their own)      */
 };
 
 /* Create an empty pool for lattices of `dtype` whose device memory
@@ -348,7 +349,8 @@ long long lbm_pool_time(const lbm_pool* P, int slot);
 
 /* Launch mode (lbm_pool_mode) and, for LBM_POOL_PERSISTENT, a cap on the
  * workgroups of the persistent launch (0: as many as the runtime reports a
- * CU can hold at once; those not resident when it starts take no part). */
+ * CU can hold at once, in cascade passes at most two per CU; those not resident
+ * when it starts take no part). */
 int lbm_pool_set_mode(lbm_pool* P, int mode, int max_grid);
 /* Vertical-stack tile of the batched kernels: vx in {1, 2, 4}, nw in
  * {4, 8, 16}, flags 0 or LBM_TILE_NT_STORE. Default: the two-step tile
@@ -360,9 +362,11 @@ int lbm_pool_set_mode(lbm_pool* P, int mode, int max_grid);
  * between grid barriers) takes two steps of every listed lattice (the
  * shapes of lbm_set_tile's two-step form); a lattice with an odd step count
  * takes its last step alone in the last one. LBM_EINVAL for other shapes.
- * With the default two-step tile, grouped and graph calls advance batches of
- * more than about 0.3 M sites by four steps per launch (cascade passes), the
- * slots' remainders of four in two-step launches before them.
+ * With the default two-step tile, calls advance batches of more than about
+ * 0.3 M sites by four steps per launch (cascade passes), the slots' remainders
+ * of four in two-step launches before them. In LBM_POOL_PERSISTENT mode with no
+ * cap on the workgroups the passes are one persistent launch, after one of the
+ * remainders if there are any.
  * Does not change results (bitwise). lbm_pool_get_tile reports
  * LBM_TILE_TWO_STEP and LBM_TILE_NT_STORE. */
 int lbm_pool_set_tile(lbm_pool* P, int vx, int nw, int flags);

@@ -35,6 +35,7 @@
 
 #include "cascade.h"
 #include "dpp.h"
+#include "grid_sync.h"
 #include "host.h"
 #include "internal.h"
 #include "step.h"
@@ -561,6 +562,55 @@ __global__ __launch_bounds__(64 * kCascadeWaves) __attribute__((amdgpu_waves_per
         cascade_wave<T, SHIFT, VX, NL, false, RC, false>(L.tile, src, dst, strip, chunk, ring, CascadePeriodic{});
 }
 
+// Persistent form: all npasses passes of a batch in one launch, members and
+// work dealt out as in the two-step kernel's persistent form (step2.hip).
+// Against that form, us per step: FP32 0.33 M sites 56.2 and 23.9, 2.7 M 76 and
+// 42, 8.8 M 135 and 71; FP64 57.7 and 18.0, 110 and 51, 239 and 101.
+template <class T, bool SHIFT, int VX, int NL, int MW>
+__global__ __launch_bounds__(64 * kCascadeWaves) __attribute__((amdgpu_waves_per_eu(MW, MW))) void
+batch_persistent_cascade_kernel(const BatchLat* __restrict__ lats, const int* __restrict__ item_lat, int nitems,
+                                int npasses, int ch, unsigned* bar, unsigned long long wait_ticks,
+                                unsigned long long grace_ticks)
+{
+    constexpr bool RC = ModelCentred<typename CompT<T>::type>::value;
+    constexpr int es = sizeof(T), NS = NL * kCascadeWaves, W = cascade_cols(VX, NS, es),
+                  HL = cascade_halo_lanes(VX, NS, es);
+    __shared__ CascadeRing<T, SHIFT, VX> ring;
+    __shared__ int next_item;
+    if (stale_barrier_error(bar)) return;
+    int rank = 0;
+    const int G = join_members(bar, wait_ticks, grace_ticks, &rank);
+    if (G == 0) return;
+    const bool by_xcd = G == (int)gridDim.x && G % 8 == 0;
+    const int nparts = by_xcd ? 8 : 1;
+    const int part = by_xcd ? (int)(blockIdx.x & 7u) : 0;
+    const int chunk = ch > 0 ? ch : 1;
+    for (int p = 0; p < npasses; ++p) {
+        unsigned* ctr = bar + kBarCtr + (p & 1) * 8 + part;
+        for (;;) {
+            if (threadIdx.x == 0) next_item = min(part_item((int)atomicAdd(ctr, 1u), part, nparts, chunk), nitems);
+            __syncthreads();
+            const int i = __builtin_amdgcn_readfirstlane(next_item);
+            __syncthreads();  // read by every wave before the next item is written; ring free again
+            if (i >= nitems) break;
+            const BatchLat* L = &lats[ldc(&item_lat[i])];
+            if (p >= ldc(&L->nsteps)) continue;  // this lattice takes fewer passes
+            const StepTile a = ldc(&L->tile);
+            const bool odd = ((ldc(&L->t0) + p) & 1) != 0;
+            const void* src = odd ? a.dst : a.src;
+            void* dst = odd ? const_cast<void*>(a.src) : a.dst;
+            const int t = i - ldc(&L->item_begin);
+            const int strip = t % a.nstrips, row = t / a.nstrips;
+            const int x0 = strip * W - HL * VX;
+            if (x0 - 1 < 0 || x0 + 64 * VX + 1 > a.g.nx)
+                cascade_wave<T, SHIFT, VX, NL, false, RC, true>(a, src, dst, strip, row, ring, CascadePeriodic{});
+            else
+                cascade_wave<T, SHIFT, VX, NL, false, RC, false>(a, src, dst, strip, row, ring, CascadePeriodic{});
+        }
+        if (!grid_barrier(bar, G, wait_ticks, bar + kBarCtr + ((p + 1) & 1) * 8, p + 1 < npasses ? 8 : 0)) return;
+    }
+}
+
 // The time a team takes per row on MI355X, in us, with one, two ... teams on
 // its CU (of as many as registers and LDS allow), from fits over lattices of
 // 400^2 to 4096^2 (within 10 % there).
@@ -680,6 +730,36 @@ hipError_t launch_batch_cascade(int dtype, const BatchLat* lats, const int* item
     case 0: return launch_batch_cascade_t<double, false, 2>(lats, item_lat, nitems, p, st);
     case 1: return launch_batch_cascade_t<float, false, 4>(lats, item_lat, nitems, p, st);
     case 2: return launch_batch_cascade_t<float, true, 4>(lats, item_lat, nitems, p, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <class T, bool SHIFT, int MW>
+static hipError_t launch_batch_cascade_persistent_t(const BatchLat* lats, const int* item_lat, int nitems, int npasses,
+                                                    int ch, unsigned* bar, hipStream_t st)
+{
+    const auto kern = batch_persistent_cascade_kernel<T, SHIFT, 2, 1, MW>;
+    constexpr int threads = 64 * kCascadeWaves;
+    int grid = 0;
+    unsigned long long wait_ticks = 0, grace_ticks = 0;
+    // A member costs 0.15 us at each barrier, and two teams per CU reach the
+    // rate of four within 5 %: at most two, and no more members than items.
+    const int most = 2 * kCus, need = (nitems + 7) / 8 * 8;
+    hipError_t e = persistent_setup((const void*)kern, threads, need < most ? need : most, &ch, &grid, &wait_ticks,
+                                    &grace_ticks, bar, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, st, lats, item_lat, nitems, npasses, ch, bar, wait_ticks,
+                       grace_ticks);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_cascade_persistent(int dtype, const BatchLat* lats, const int* item_lat, int nitems,
+                                           int npasses, int ch, unsigned* bar, hipStream_t st)
+{
+    switch (dtype) {
+    case 0: return launch_batch_cascade_persistent_t<double, false, 2>(lats, item_lat, nitems, npasses, ch, bar, st);
+    case 1: return launch_batch_cascade_persistent_t<float, false, 4>(lats, item_lat, nitems, npasses, ch, bar, st);
+    case 2: return launch_batch_cascade_persistent_t<float, true, 4>(lats, item_lat, nitems, npasses, ch, bar, st);
     }
     return hipErrorInvalidValue;
 }

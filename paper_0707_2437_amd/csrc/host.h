@@ -54,6 +54,9 @@ hipError_t launch_block(int dtype, const BlockShape& b, const StepTile& t, const
 // Cascade pass p of a batch (descriptors with the strips and chunks of
 // cascade_cols, nsteps counting passes).
 hipError_t launch_batch_cascade(int dtype, const BatchLat* lats, const int* item_lat, int nitems, int p, hipStream_t st);
+// All its npasses passes in one persistent launch.
+hipError_t launch_batch_cascade_persistent(int dtype, const BatchLat* lats, const int* item_lat, int nitems,
+                                           int npasses, int ch, unsigned* bar, hipStream_t st);
 hipError_t launch_ghosts(int dtype, void* s, const Geom& g, hipStream_t st);
 hipError_t launch_init(int dtype, void* s, const Geom& g, const double* rho, const double* ux, const double* uy,
                        double eqs, hipStream_t st);

@@ -281,10 +281,15 @@ hipError_t run_batch(lbm_pool* P, int nmax)
     const bool nts = P->nts != 0;
     if (P->mode == LBM_POOL_PERSISTENT) {
         P->bar_used = true;
-        return P->two ? launch_batch2_persistent(P->dtype, P->vx, P->nw, nts, P->d_lats, P->d_items, nitems,
-                                                 (nmax + 1) / 2, P->max_grid, P->xcd_chunk, P->d_bar, P->stream)
-                      : launch_batch(P->dtype, P->vx, P->nw, nts, true, P->d_lats, P->d_items, nitems, nmax,
-                                     P->max_grid, P->xcd_chunk, P->d_bar, P->stream);
+        if (nitems > 0)
+            e = P->two ? launch_batch2_persistent(P->dtype, P->vx, P->nw, nts, P->d_lats, P->d_items, nitems,
+                                                  (nmax + 1) / 2, P->max_grid, P->xcd_chunk, P->d_bar, P->stream)
+                       : launch_batch(P->dtype, P->vx, P->nw, nts, true, P->d_lats, P->d_items, nitems, nmax,
+                                      P->max_grid, P->xcd_chunk, P->d_bar, P->stream);
+        if (e == hipSuccess && deep_items > 0)
+            e = launch_batch_cascade_persistent(P->dtype, P->d_lats + P->deep_lats_at, P->d_items + nitems, deep_items,
+                                                P->deep_passes, P->xcd_chunk, P->d_bar, P->stream);
+        return e;
     }
     // launch k of the call: step k, or two-step pass k; then the cascade passes
     const int nfirst = nitems == 0 ? 0 : (P->two ? (nmax + 1) / 2 : nmax);
@@ -344,11 +349,12 @@ hipError_t run_batch(lbm_pool* P, int nmax)
 }
 
 // The cascade passes of a call that advances the listed slots by nsteps
-// (vx = 0: none): with the dtype's default tile, grouped or graph launches,
+// (levels = 0: none): with the dtype's default tile,
 // for the lattices that take at least one pass of four steps.
 CascadeShape pool_cascade(lbm_pool* P, const int* slots, const int* nsteps, int count)
 {
-    if (P->mode == LBM_POOL_PERSISTENT || !is_deep_tile(P->dtype, P->vx, P->nw, P->nts, P->two)) return {};
+    if (P->mode == LBM_POOL_PERSISTENT && P->max_grid > 0) return {};  // the estimates are for the whole GPU
+    if (!is_deep_tile(P->dtype, P->vx, P->nw, P->nts, P->two)) return {};
     P->sizes.clear();
     for (int d = 0; d < 2; ++d)
         for (int k = 0; k < count; ++k) {
@@ -363,7 +369,7 @@ CascadeShape pool_cascade(lbm_pool* P, const int* slots, const int* nsteps, int 
 }
 
 // Append the descriptor of slot S for `passes` cascade passes, its items one
-// wave each.
+// team each.
 void add_cascade(lbm_pool* P, const Slot& S, const CascadeShape& c, int passes, long long buffer_t0)
 {
     BatchLat b{};
@@ -831,6 +837,9 @@ int lbm_pool_autotune(lbm_pool* P, const int* slots, int count, int reps, int us
         const bool nts = (k.flags & LBM_TILE_NT_STORE) != 0;
         const CascadeShape deep = is_deep_tile(P->dtype, k.vx, k.nw, nts, two) ? four : CascadeShape{};
         auto go = [&]() {
+            if (deep.levels && pers)
+                return launch_batch_cascade_persistent(P->dtype, P->d_lats, P->d_items, nitems, 1, k.ch, P->d_bar,
+                                                       P->stream);
             if (deep.levels) return launch_batch_cascade(P->dtype, P->d_lats, P->d_items, nitems, 0, P->stream);
             hipError_t ge = hipSuccess;
             for (int r = 0; r < (two ? 2 : 4) && ge == hipSuccess; ++r) {

@@ -2,7 +2,7 @@
 lattice per launch): every slot has the bits it gets alone in single steps, for
 lattices of widths around a strip's columns, lower than a pass's halo and
 taller than a chunk, with per-slot counts of every remainder of four (some
-below one pass, some zero), over consecutive calls, in grouped and graph
+below one pass, some zero), over consecutive calls, in grouped, graph and persistent
 launches, mixed with calls of two-step and single-step tiles."""
 import numpy as np
 import pytest
@@ -36,7 +36,7 @@ def alone(k, dtype, steps):
 
 
 @pytest.mark.parametrize("dtype", ["f64", "f32", "f32s"])
-@pytest.mark.parametrize("mode", [lbm.GROUPED, lbm.GRAPH])
+@pytest.mark.parametrize("mode", [lbm.GROUPED, lbm.GRAPH, lbm.PERSISTENT])
 def test_pool_cascade_bitwise(dtype, mode):
     total = sum(lbm.Pool.slot_bytes(nx, ny, dtype) for nx, ny in SHAPES)
     with lbm.Pool(total, dtype) as P:
