@@ -633,7 +633,11 @@ static double cascade_time(const CascadeCost& c, double teams, int h)
     const int rounds = (int)(teams / slots);
     const int left = (int)((teams - rounds * slots + kCus - 1) / kCus);
     const int rows = h + 2 * cascade_halo(c.levels * kCascadeWaves) + kCascadeWaves - 1;
-    return rows * (rounds * c.row[c.teams - 1] + (left ? c.row[left - 1] : 0.0));
+    const double t = rows * (rounds * c.row[c.teams - 1] + (left ? c.row[left - 1] : 0.0));
+    // FP16 strips at an edge load and store two bytes at a time and take half
+    // as long again; the fewer teams a CU sees, the less others fill in
+    // (8192^2: one round of 394 rows 211 us per step, three of 130 rows 185)
+    return c.dtype == 3 ? t + rows * c.row[c.teams - 1] * 0.5 / (rounds + (left > 0)) : t;
 }
 
 // 18 planes of the state pass the caches at 5.2 bytes per ps from HBM; a state
