@@ -172,6 +172,12 @@ template <int VX> struct CascadeRow<_Float16, true, VX> {
 // densities w), the densities of the row above it (wp), and the planes of
 // its last results that wait for rows below: e_iy = 0 of the last row (z),
 // e_iy = 1 of the last two (up, by the row's parity).
+// A row's columns of a lane in LDS, as one aligned vector: as a struct of
+// 4-byte alignment they move in halves, with four bank conflicts each.
+template <int BYTES> struct CascadeLds {
+    typedef unsigned type __attribute__((ext_vector_type(BYTES / 4)));
+};
+
 // Stands for XbcValues where the lattice is periodic in x.
 struct CascadePeriodic {};
 
@@ -211,8 +217,8 @@ __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t rs, const V v, 
 // (Sec. 4: periodic in x) and store element by element.
 template <class T, bool SHIFT, int VX, int NL, bool FIRST, bool LAST, bool FIELD, bool RC, bool EDGE, class XB>
 __device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src, void* dst, int strip, int chunk,
-                                             [[maybe_unused]] typename CascadeRow<T, SHIFT, VX>::Mem (*in)[9][64],
-                                             [[maybe_unused]] typename CascadeRow<T, SHIFT, VX>::Mem (*outq)[9][64],
+                                             [[maybe_unused]] typename CascadeLds<sizeof(T) * VX>::type (*in)[9][64],
+                                             [[maybe_unused]] typename CascadeLds<sizeof(T) * VX>::type (*outq)[9][64],
                                              int w, [[maybe_unused]] const XB& xb)
 {
     using C = typename CompT<T>::type;
@@ -386,7 +392,7 @@ __device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src,
             land(raw, nd);
         } else {
             Mem m[9];
-            static_for<0, 9>([&](auto ic) { m[decltype(ic)::value] = in[P][decltype(ic)::value][lane]; });
+            static_for<0, 9>([&](auto ic) { m[decltype(ic)::value] = __builtin_bit_cast(Mem, in[P][decltype(ic)::value][lane]); });
             R q[9];
             land(m, q);
             gather(parity, gate, q, nd);
@@ -453,7 +459,10 @@ __device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src,
             } else if constexpr (LAST) {
                 write(kk, f);
             } else {
-                static_for<0, 9>([&](auto ic) { outq[P][decltype(ic)::value][lane] = f[decltype(ic)::value]; });
+                using Lds = typename CascadeLds<sizeof(Mem)>::type;
+                static_for<0, 9>([&](auto ic) {
+                    outq[P][decltype(ic)::value][lane] = __builtin_bit_cast(Lds, f[decltype(ic)::value]);
+                });
             }
         });
         meet();
@@ -494,7 +503,7 @@ hipError_t launch_ghosts(int dtype, void* s, const Geom& g, hipStream_t st)
 
 // Between the waves of a team: the last two rows each hands to the next.
 template <class T, bool SHIFT, int VX> struct CascadeRing {
-    typename CascadeRow<T, SHIFT, VX>::Mem row[kCascadeWaves - 1][2][9][64];
+    typename CascadeLds<sizeof(T) * VX>::type row[kCascadeWaves - 1][2][9][64];
 };
 
 // One wave of a team. The waves pass the same number of barriers: a wave's
