@@ -642,11 +642,7 @@ static double cascade_time(const CascadeCost& c, double teams, int h)
     const int rounds = (int)(teams / slots);
     const int left = (int)((teams - rounds * slots + kCus - 1) / kCus);
     const int rows = h + 2 * cascade_halo(c.levels * kCascadeWaves) + kCascadeWaves - 1;
-    const double t = rows * (rounds * c.row[c.teams - 1] + (left ? c.row[left - 1] : 0.0));
-    // FP16 strips at an edge load and store two bytes at a time and take half
-    // as long again; the fewer teams a CU sees, the less others fill in
-    // (8192^2: one round of 394 rows 211 us per step, three of 130 rows 185)
-    return c.dtype == 3 ? t + rows * c.row[c.teams - 1] * 0.5 / (rounds + (left > 0)) : t;
+    return rows * (rounds * c.row[c.teams - 1] + (left ? c.row[left - 1] : 0.0));
 }
 
 // 18 planes of the state pass the caches at 5.2 bytes per ps from HBM; a state
@@ -669,6 +665,10 @@ void cascade_shapes(int dtype, int nx, int ny, bool inlet, CascadeShape out[2])
     static const double two_step[4][2] = {{2.4, 14.9}, {2.6, 7.4}, {2.6, 7.4}, {2.8, 4.7}};
     const int es = dtype == 0 ? 8 : (dtype == 3 ? 2 : 4);
     const double sites = (double)nx * ny, per_us = cascade_bytes_per_us(sites * 18 * es);
+    // FP16 strips at an edge load and store two bytes at a time and take half as
+    // long again: with tall chunks they end alone (8192^2, us per step: 394
+    // rows 211, 194 rows 202, 130 rows 185)
+    const int most = dtype == 3 ? 160 : 400;
     // us per step of the best so far; with an inlet, single steps and a launch
     // for the boundary after each
     double t_best = inlet ? 4.5 + 2.3 * es * sites * 1e-6 : two_step[dtype][0] + two_step[dtype][1] * sites * 1e-6;
@@ -678,7 +678,7 @@ void cascade_shapes(int dtype, int nx, int ny, bool inlet, CascadeShape out[2])
         for (const CascadeCost& c : kCosts) {
             if (c.dtype != dtype || c.levels != levels) continue;
             const int w = cascade_cols(cascade_vx(dtype), ns, es), strips = (nx + w - 1) / w;
-            for (int h = 6; h < ny + 4 && h < 400; h += 4) {
+            for (int h = 6; h < ny + 4 && h < most; h += 4) {
                 const int chunks = (ny + h - 1) / h;
                 const double work = 1.0 + cascade_time(c, (double)strips * chunks, h);
                 const double bytes = 9.0 * es * nx * (1.15 * chunks * (h + warm) + ny);
