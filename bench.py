@@ -29,8 +29,13 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBS = 8000.0  # MI355X HBM3E
-# rocprofv3 counter records of the FP32 4096^2 launches: the two-step and single-step kernels
-TRAFFIC_RECORDS = {"step2": os.path.join(ROOT, "profiles", "step2_f32_4096_traffic.json"),
+# VALU lane-instructions: 256 CUs of 4 SIMDs, 16 lanes a cycle each at 2.4 GHz; and per site and step of the
+# FP32 cascade kernel's inner loop
+PEAK_VALU = 256 * 4 * 16 * 2.4e9
+VALU_PER_SITE = 80.5
+# rocprofv3 counter records of the FP32 4096^2 launches: the cascade, two-step and single-step kernels
+TRAFFIC_RECORDS = {"cascade": os.path.join(ROOT, "profiles", "cascade_f32_4096_traffic.json"),
+                   "step2": os.path.join(ROOT, "profiles", "step2_f32_4096_traffic.json"),
                    "step": os.path.join(ROOT, "profiles", "step_f32_4096_traffic.json")}
 TWO_STEP = 32  # LBM_TILE_TWO_STEP
 BYTES_PER_SITE = {"f64": 144, "f32": 72, "f32s": 72, "f16s": 36}  # 9 reads + 9 writes
@@ -101,19 +106,41 @@ def make_sweep(lbm, workloads, torch, n, form, stream):
     return lattices
 
 
-def launches_of(tile, steps):
+def cascade_steps(form, n):
+    """Most steps per cascade pass of an n x n lattice in the form's default
+    shape, for the sizes measured here (n >= 2048): eight, four with a c^2
+    field or in FP16 storage; below, none is assumed."""
+    dtype, variant = form_parts(form)
+    return 0 if n < 2048 else (4 if variant == "field" or dtype == "f16s" else 8)
+
+
+def launches_of(tile, steps, deep=0):
     """Kernel launches lbm_step makes for `steps` steps in this shape: two
-    steps per launch for a two-step shape (a lone last step takes one more)."""
-    return (steps + 1) // 2 if tile[3] & TWO_STEP else steps
+    steps per launch for a two-step shape (a lone last step takes one more),
+    cascade passes of at most `deep` steps first."""
+    n = 0
+    for p in (8, 4):
+        if p <= deep:
+            n += steps // p
+            steps %= p
+    return n + ((steps + 1) // 2 if tile[3] & TWO_STEP else steps)
+
+
+def sweep_launches(tile, steps, deep=0):
+    """The same for time_sweep's calls of CALL_STEPS steps."""
+    return steps // CALL_STEPS * launches_of(tile, CALL_STEPS, deep) + launches_of(tile, steps % CALL_STEPS, deep)
+
+
+CALL_STEPS = 8
 
 
 def time_sweep(torch, lattices, steps, warmup, stream):
-    # Steps are taken two at a time per lattice (one two-step launch, or two
-    # single-step launches), lattice after lattice.
+    # Steps are taken eight at a time per lattice (one or two cascade passes,
+    # or two-step or single-step launches), lattice after lattice.
     def run(k):
-        for s in range(0, k, 2):
+        for s in range(0, k, CALL_STEPS):
             for L in lattices:
-                L.step(min(2, k - s))
+                L.step(min(CALL_STEPS, k - s))
     run(warmup)
     torch.cuda.synchronize()
     e0 = torch.cuda.Event(enable_timing=True)
@@ -127,10 +154,13 @@ def time_sweep(torch, lattices, steps, warmup, stream):
     return e0.elapsed_time(e1) / 1e3, wall
 
 
-def kernel_name(tile, form):
+def kernel_name(tile, form, deep=0):
     vx, nw, h, flags = tile
     dtype, variant = form_parts(form)
     t = {"f64": "double,false", "f32": "float,false", "f32s": "float,true", "f16s": "_Float16,true"}[dtype]
+    if deep:
+        return (f"lbm::cascade_kernel<{t},{4 if dtype == 'f16s' else 2},{deep // 4},"
+                f"{'field' if variant == 'field' else 'nofield'}>")
     if flags & TWO_STEP:
         return (f"lbm::step2_vstack_kernel<{t},{vx},{nw},{'true' if flags & 2 else 'false'},"
                 f"{'true' if variant == 'field' else 'false'}>")
@@ -143,9 +173,9 @@ def kernel_name(tile, form):
 
 def measured_traffic(kernel, n):
     """HBM bytes per launch from the committed rocprofv3 counter record of
-    this kernel (two-step or single-step), if it was taken on the current
-    kernel source and kernel; else None."""
-    which = "step2" if kernel.startswith("lbm::step2_") else "step"
+    this kernel (cascade, two-step or single-step), if it was taken on the
+    current kernel source and kernel; else None."""
+    which = next((w for w in ("cascade", "step2") if kernel.startswith(f"lbm::{w}_")), "step")
     try:
         from paper_0707_2437_amd import profiling
         rec = json.load(open(TRAFFIC_RECORDS[which]))
@@ -161,6 +191,7 @@ def measure_form(lbm, workloads, torch, n, dtype, steps, warmup, tile=None):
     # all launches go to one dedicated stream; the HIP events are recorded on it
     stream = torch.cuda.Stream()
     lats = make_sweep(lbm, workloads, torch, n, dtype, stream)
+    deep = cascade_steps(dtype, n) if tile is None else 0
     if tile is not None:
         for L in lats:
             L.set_tile(*tile)
@@ -171,12 +202,12 @@ def measure_form(lbm, workloads, torch, n, dtype, steps, warmup, tile=None):
         L.close()
     sites = n * n * len(lats)
     # every launch reads and writes each site's nine populations once
-    launches = launches_of(tile, steps) * len(lats)
+    launches = sweep_launches(tile, steps, deep) * len(lats)
     mlups = sites * steps / sec / 1e6
     gbs = form_bytes_per_site(dtype) * n * n / (sec / launches) / 1e9
     return {"mlups": mlups, "ms_per_step": 1e3 * sec / steps, "kernel_us": 1e6 * sec / launches,
             "achieved_GBs": gbs, "frac": gbs / PEAK_HBM_GBS, "wall_s": wall,
-            "mass_total_first": tot[0][0], "kernel": kernel_name(tile, dtype), "tile": list(tile)}
+            "mass_total_first": tot[0][0], "kernel": kernel_name(tile, dtype, deep), "tile": list(tile)}
 
 
 def cpu_model():
@@ -307,10 +338,9 @@ def measure_batched(lbm, workloads, torch, nlat, steps, mode, warmup=5, persiste
         pers = sites * persistent_steps / (e0.elapsed_time(e1) / 1e3) / 1e6  # single steps (72 B per update)
         pers_members = P.persistent_members()
     P.close()
-    # plain kernel, the lattices one at a time, two steps per call (the
-    # single-lattice default shape: one two-step launch per lattice per two
-    # steps; same lattices, fewer steps)
-    psteps = max(2, steps // 10) // 2 * 2
+    # plain kernel, the lattices one at a time, eight steps per call (the
+    # single-lattice default shape; same lattices, fewer steps)
+    psteps = max(CALL_STEPS, steps // 10) // CALL_STEPS * CALL_STEPS
     lats = []
     for sp in specs:
         L = lbm.Lattice(sp["nx"], sp["ny"], sp["tau"], sp["c2"], "f32")
@@ -321,9 +351,9 @@ def measure_batched(lbm, workloads, torch, nlat, steps, mode, warmup=5, persiste
         L.step(warmup)
     torch.cuda.synchronize()
     e0.record(stream)
-    for _ in range(psteps // 2):
+    for _ in range(psteps // CALL_STEPS):
         for L in lats:
-            L.step(2)
+            L.step(CALL_STEPS)
     e1.record(stream)
     torch.cuda.synchronize()
     psec = e0.elapsed_time(e1) / 1e3
@@ -331,9 +361,11 @@ def measure_batched(lbm, workloads, torch, nlat, steps, mode, warmup=5, persiste
         L.close()
     mlups = sites * steps / sec / 1e6
     plain = sites * psteps / psec / 1e6
-    # algorithmic bytes per site update: one load and one store per launch,
-    # a two-step launch covering two updates
-    per_update = BYTES_PER_SITE["f32"] / (2 if tile[2] & TWO_STEP else 1)
+    # algorithmic bytes per site update: one load and one store per launch, a
+    # two-step launch covering two updates and a cascade pass, which batches of
+    # this size take with the default tile, four
+    two = 2 if tile[2] & TWO_STEP else 1
+    per_update = BYTES_PER_SITE["f32"] / (4 if tuple(tile) == (2, 16, TWO_STEP | 2) else two)
     return {"mlups": mlups, "frac": mlups * 1e6 * per_update / 1e9 / PEAK_HBM_GBS,
             "lattices": nlat, "sites": sites, "steps": steps, "mode": mode, "tile": list(tile),
             "seconds": sec, "plain_mlups": plain, "vs_plain": mlups / plain, "nonfinite_lattices": nonfinite,
@@ -381,9 +413,10 @@ def measure_precision(lbm, workloads, torch, steps, warmup=5, n=8192):
         tile = L.get_tile()
         L.close()
         mlups = n * n * steps / sec / 1e6
-        gbs = form_bytes_per_site(dtype) * n * n * launches_of(tile, steps) / sec / 1e9
+        deep = cascade_steps(dtype, n)
+        gbs = form_bytes_per_site(dtype) * n * n * sweep_launches(tile, steps, deep) / sec / 1e9
         out[dtype] = {"mlups": mlups, "achieved_GBs": gbs, "frac": gbs / PEAK_HBM_GBS, "steps": steps,
-                      "kernel": kernel_name(tile, dtype), "lattice": [n, n]}
+                      "kernel": kernel_name(tile, dtype, deep), "lattice": [n, n]}
     return out
 
 
@@ -496,8 +529,11 @@ def main():
                    "lattice": [n, n], "lattices_per_step": len(sweep), "tau": 0.6,
                    "c2": [round(c, 6) for c in sweep],
                    "init": "plane sound wave amp 1e-3 + uniform density noise 1e-4 (seeded)"},
-        "roofline": {"bound": "hbm", "achieved": round(head["achieved_GBs"], 1), "peak": PEAK_HBM_GBS,
-                     "unit": "GB/s", "frac": round(head["frac"], 4),
+        "roofline": {"bound": "valu", "achieved": round(head["mlups"] * 1e6 * VALU_PER_SITE / 1e12, 2),
+                     "peak": round(PEAK_VALU / 1e12, 1), "unit": "T lane-instructions/s (halo sites not counted)",
+                     "frac": round(head["mlups"] * 1e6 * VALU_PER_SITE / PEAK_VALU, 4),
+                     "hbm": {"achieved": round(head["achieved_GBs"], 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                             "frac": round(head["frac"], 4)},
                      "traffic": measured_traffic(head["kernel"], n),
                      "kernel": head["kernel"],
                      "bytes_per_launch": BYTES_PER_SITE["f32"] * n * n,
