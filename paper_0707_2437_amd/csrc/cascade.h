@@ -20,8 +20,8 @@ constexpr int cascade_halo(int ns) { return 2 * ns - 1; }
 // 112 columns move 1.42 GB in 262 us, strips of 120 columns or strips
 // shifted by half a block 1.3-1.4 GB in 349-356 us. FP16 rows hold half the
 // bytes and their pass is bound by instructions: half blocks cost it less
-// than the lanes that whole ones would idle (8192^2: 205 us per step with
-// strips of 112 columns, 218 with 96).
+// than the lanes that whole ones would idle (8192^2, two columns per lane in
+// one wave: 205 us per step with strips of 112 columns, 218 with 96).
 constexpr int cascade_halo_lanes(int vx, int ns, int es)
 {
     int hl = (cascade_halo(ns) + vx - 1) / vx;

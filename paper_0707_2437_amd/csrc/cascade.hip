@@ -677,6 +677,7 @@ void cascade_shapes(int dtype, int nx, int ny, bool inlet, CascadeShape out[2])
         const int ns = levels * kCascadeWaves, warm = 2 * cascade_halo(ns);
         for (const CascadeCost& c : kCosts) {
             if (c.dtype != dtype || c.levels != levels) continue;
+            if (c.row[0] * (6 + warm) / ns >= t_best) continue;  // slower with every height (saves the search)
             const int w = cascade_cols(cascade_vx(dtype), ns, es), strips = (nx + w - 1) / w;
             for (int h = 6; h < ny + 4 && h < most; h += 4) {
                 const int chunks = (ny + h - 1) / h;

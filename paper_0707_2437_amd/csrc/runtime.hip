@@ -292,7 +292,7 @@ lbm_lattice* lbm_create(int nx, int ny, double tau, double c2, int dtype)
     L->h = td.h;
     L->kflags = td.flags;
     apply_tile_env(dtype, &L->vx, &L->nw, &L->h, &L->kflags);
-    for (int k = 0; k < 2; ++k) lbm::cascade_shapes(dtype, nx, ny, k == 1, L->deep[k]);
+    lbm::cascade_shapes(dtype, nx, ny, false, L->deep[0]);
     hipError_t e = hipGetDevice(&L->device);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&L->own, hipStreamNonBlocking);
     if (e != hipSuccess) {
@@ -461,6 +461,7 @@ int lbm_set_x_boundaries(lbm_lattice* L, int mode, double amplitude, double peri
     if (mode != LBM_XBC_INLET_OUTLET || L->nx < 5 || !std::isfinite(period) || !(period > 0.0) ||
         !std::isfinite(amplitude) || !(std::fabs(amplitude) < 1.0))
         return LBM_EINVAL;
+    cascade_shapes(L->dtype, L->nx, L->ny, true, L->deep[1]);
     L->xbc = mode;
     L->amp = amplitude;
     L->period = period;

@@ -44,9 +44,10 @@ struct Ring {
     hipEvent_t ev[kSlots] = {};
 };
 
-// What outlives one call: at most kKeepRings rings, one page of totals and
-// kKeepScratch bytes of device scratch per device, while any lattice or pool
-// lives.
+// What outlives one call: at most kKeepRings rings and kKeepScratch bytes of
+// device scratch per device, while any lattice or pool lives; and one page of
+// totals, whose lines are given back to it (a page freed with the last object
+// costs the next one 50 us to 1 ms).
 std::mutex g_lock;
 int g_users = 0;
 constexpr int kLines = 64;           // of a page, 64 bytes each
@@ -250,12 +251,9 @@ void staging_retain()
 void staging_release()
 {
     Ring gone[kKeepRings];
-    char* page;
     {
         std::lock_guard<std::mutex> hold(g_lock);
         if (--g_users > 0) return;
-        page = g_page;
-        g_page = nullptr;
         for (int k = 0; k < kKeepRings; ++k) {
             gone[k] = g_kept[k];
             g_kept[k] = Ring();
@@ -264,7 +262,6 @@ void staging_release()
             if (m) (void)hipMemPoolTrimTo(m, 0);
     }
     for (Ring& r : gone) free_ring(r);
-    if (page) (void)hipHostFree(page);
 }
 
 // A line of the page, or memory of its own beyond kLines objects: an
