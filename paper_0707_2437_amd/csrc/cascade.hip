@@ -19,18 +19,19 @@
 // Bound: one load and one store of the state per NS steps, against 59
 // operations per site and step (77 with the FP32 form's conversions, 80 with
 // the lane shifts), and the halo: 2 NS - 1 columns at each side of a strip
-// and as many rows before a chunk. FP32 at 4096^2, eight steps: 477 us per
-// pass, of which the instructions (halo included) need 400 and the bare
+// and as many rows before a chunk. FP32 at 4096^2, eight steps: 467 us per
+// pass, of which the instructions (halo included) need 415 and the bare
 // access pattern 262. With four steps the access pattern bounds the pass (280
 // us), so large lattices take eight; FP16 moves half the bytes and stays at
 // four. All levels in one wave, without LDS, was the form before: its
 // registers (250) allow two waves per SIMD and chunks have to be a quarter as
 // high to fill the GPU, so that the halo rows weigh four times as much.
 // Measured per step, two-step kernel / one wave / team: FP32 4096^2 121.7 /
-// 68.9 / 59.6 us, FP32S 121 / 71.7 / 50.1, FP64 240.5 / 127.7 / 111.6, FP16
-// 8192^2 389 / 217 / 186, FP32 1000 x 777 8.9 / 7.2 / 6.5, with a c2 field
-// 9.2 / 8.6 / 6.9. A team of eight waves of one level each: 61.1 us FP32, 53.5
-// FP32S, 112.2 FP64.
+// 68.9 / 58.4 us, FP32S 121 / 71.7 / 50.3, FP64 240.5 / 127.7 / 103.5, FP16
+// 8192^2 389 / 217 / 183, FP32 1000 x 777 8.9 / 7.2 / 5.85, with a c2 field
+// 9.2 / 8.6 / 6.2. A team of eight waves of one level each (before the rows
+// moved as aligned vectors): 61.1 us FP32 against 59.6, 53.5 FP32S against
+// 50.1, 112.2 FP64 against 111.6.
 #include <hip/hip_runtime.h>
 
 #include "cascade.h"
