@@ -38,6 +38,34 @@ constexpr int kKeepRings = 2;
 constexpr size_t kKeepScratch = (size_t)256 << 20;
 constexpr int kMaxDevices = 16;
 
+// The device of stream st's work (of the null stream: the current one), which
+// need not be the calling thread's current device.
+hipError_t stream_device(hipStream_t st, int* device)
+{
+    hipDevice_t d = 0;
+    if (st && hipStreamGetDevice(st, &d) == hipSuccess) {
+        *device = d;
+        return hipSuccess;
+    }
+    return hipGetDevice(device);
+}
+
+// Makes a device current for its life.
+struct OnDevice {
+    int before = -1;
+    hipError_t e;
+    explicit OnDevice(int device)
+    {
+        e = hipGetDevice(&before);
+        if (e == hipSuccess && before == device) before = -1;
+        else if (e == hipSuccess) e = hipSetDevice(device);
+    }
+    ~OnDevice()
+    {
+        if (before >= 0) (void)hipSetDevice(before);
+    }
+};
+
 struct Ring {
     char* p = nullptr;
     int device = -1;
@@ -67,11 +95,8 @@ void free_ring(Ring& r)
 struct RingLease {
     Ring r;
     bool sound = false;  // every call on it succeeded
-    hipError_t take()
+    hipError_t take(int device)  // events are recorded on streams of their own device only
     {
-        int device = 0;
-        hipError_t e = hipGetDevice(&device);
-        if (e != hipSuccess) return e;
         {
             std::lock_guard<std::mutex> hold(g_lock);
             for (Ring& k : g_kept)
@@ -82,7 +107,9 @@ struct RingLease {
                 }
         }
         r.device = device;
-        e = hipHostMalloc((void**)&r.p, kSlots * kSlot, hipHostMallocDefault);
+        OnDevice on(device);
+        hipError_t e = on.e;
+        if (e == hipSuccess) e = hipHostMalloc((void**)&r.p, kSlots * kSlot, hipHostMallocDefault);
         if (e != hipSuccess) r.p = nullptr;
         for (hipEvent_t& ev : r.ev)
             if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
@@ -190,7 +217,9 @@ struct Shared {
 hipError_t staged(const Plan& plan, hipStream_t st)
 {
     RingLease lease;
-    hipError_t e = lease.take();
+    int device = 0;
+    hipError_t e = stream_device(st, &device);
+    if (e == hipSuccess) e = lease.take(device);
     if (e != hipSuccess) return e;
     Shared sh(plan, lease.r.p);
     int sent = 0;
@@ -304,7 +333,7 @@ hipError_t scratch_alloc(void** p, size_t bytes, hipStream_t st)
 {
     *p = nullptr;
     int device = 0;
-    hipError_t e = hipGetDevice(&device);
+    hipError_t e = stream_device(st, &device);
     hipMemPool_t m = nullptr;
     if (e == hipSuccess && device < kMaxDevices) {
         std::lock_guard<std::mutex> hold(g_lock);
