@@ -20,6 +20,8 @@ def test_calls_with_another_device_current(so):
 L = lbm.Lattice(700, 900, 0.7, 0.3, "f64")
 P = lbm.Pool(1 << 30, "f32")
 s = P.add(800, 900, 0.7, 0.3)
+P.init(s, None, None, None)
+P.step([s], 4)
 assert fake.hipSetDevice(1) == 0
 used = fake.fake_used(1)
 fake.fake_log()
