@@ -301,6 +301,9 @@ void staging_release();
 hipError_t totals_alloc(double** p);
 void totals_free(double* p);
 hipError_t scratch_alloc(void** p, size_t bytes, hipStream_t st);
+// hipMalloc on the current device, which gets kept scratch back before the
+// allocation is reported as failed.
+hipError_t device_malloc(void** p, size_t bytes);
 
 // Device staging memory of one host-array entry point: taken from a
 // stream-ordered memory pool on the call's stream and given back on that

@@ -38,12 +38,12 @@ struct Slot {
     int ph = 0;
 };
 
-// Chunks of slot memory come from hipMalloc (see arena.h).
+// Chunks of slot memory come from device_malloc (see arena.h).
 struct DeviceAlloc {
     using Err = hipError_t;
     static constexpr hipError_t kOk = hipSuccess;
     static constexpr hipError_t kNoMem = hipErrorOutOfMemory;
-    static hipError_t get(void** p, size_t n) { return hipMalloc(p, n); }
+    static hipError_t get(void** p, size_t n) { return lbm::device_malloc(p, n); }
     static void put(void* p) { (void)hipFree(p); }
 };
 using SlotArena = lbm::Arena<DeviceAlloc>;
@@ -225,7 +225,7 @@ hipError_t ensure_cap(lbm_pool* P, int n, int nitems)
     if (n > P->cap) {
         int cap = std::max(n, std::max(16, 2 * P->cap));
         BatchLat* d = nullptr;
-        hipError_t e = hipMalloc((void**)&d, sizeof(BatchLat) * (size_t)cap);
+        hipError_t e = device_malloc((void**)&d, sizeof(BatchLat) * (size_t)cap);
         if (e != hipSuccess) return e;
         if (P->d_lats) {
             (void)hipStreamSynchronize(P->stream);
@@ -238,7 +238,7 @@ hipError_t ensure_cap(lbm_pool* P, int n, int nitems)
     if (nitems > P->item_cap) {
         int cap = std::max(nitems, std::max(1024, 2 * P->item_cap));
         int* d = nullptr;
-        hipError_t e = hipMalloc((void**)&d, sizeof(int) * (size_t)cap);
+        hipError_t e = device_malloc((void**)&d, sizeof(int) * (size_t)cap);
         if (e != hipSuccess) return e;
         if (P->d_items) {
             (void)hipStreamSynchronize(P->stream);
@@ -424,7 +424,7 @@ lbm_pool* lbm_pool_create(size_t budget_bytes, int dtype)
     char* noalloc_base = nullptr;  // look up lbm_pool_step_noalloc's array while set up
     if (e == hipSuccess) e = noalloc_scratch(P->device, &noalloc_base);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&P->own, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipMalloc((void**)&P->d_bar, kPoolBarWords * sizeof(unsigned));
+    if (e == hipSuccess) e = device_malloc((void**)&P->d_bar, kPoolBarWords * sizeof(unsigned));
     lbm::staging_retain();
     if (e == hipSuccess) e = lbm::totals_alloc(&P->tot);
     if (e == hipSuccess) e = hipMemsetAsync(P->d_bar, 0, kPoolBarWords * sizeof(unsigned), P->own);

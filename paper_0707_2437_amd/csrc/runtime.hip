@@ -222,7 +222,7 @@ int ensure_field(lbm_lattice* L)
 {
     if (L->field) return LBM_OK;
     void* p = nullptr;
-    hipError_t e = hipMalloc(&p, field_bytes(L->nx, L->ny, L->dtype));
+    hipError_t e = device_malloc(&p, field_bytes(L->nx, L->ny, L->dtype));
     if (e != hipSuccess) return e == hipErrorOutOfMemory ? LBM_ENOMEM : LBM_EDEVICE;
     L->field = p;
     L->fpitch = field_pitch(L->nx);
@@ -303,7 +303,7 @@ lbm_lattice* lbm_create(int nx, int ny, double tau, double c2, int dtype)
     lbm::staging_retain();
     L->stream = L->own;
     const size_t red_at = (footprint(L->g, L->esize) + 63) / 64 * 64;  // one allocation: 30 us each
-    e = hipMalloc(&L->buf, red_at + red_doubles(L->g) * sizeof(double));
+    e = device_malloc(&L->buf, red_at + red_doubles(L->g) * sizeof(double));
     if (e == hipSuccess) e = lbm::totals_alloc(&L->tot);
     if (e == hipSuccess) e = hipMemsetAsync(L->buf, 0, red_at, L->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(L->stream);

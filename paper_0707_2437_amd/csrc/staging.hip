@@ -329,6 +329,33 @@ void totals_free(double* p)
     (void)hipHostFree(p);
 }
 
+// Gives idle scratch of a device back to it: true if there may be memory that
+// was not to be had before. Waits for the device, since a block is idle only
+// when the calls that used it are done; its callers have run out of memory.
+static bool return_scratch(int device)
+{
+    hipMemPool_t m = nullptr;
+    if (device >= 0 && device < kMaxDevices) {
+        std::lock_guard<std::mutex> hold(g_lock);
+        m = g_scratch[device];
+    }
+    if (!m) return false;
+    OnDevice on(device);
+    (void)hipDeviceSynchronize();
+    const bool some = hipMemPoolTrimTo(m, 0) == hipSuccess;
+    (void)hipGetLastError();
+    return some;
+}
+
+hipError_t device_malloc(void** p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    int device = 0;
+    if (e == hipErrorOutOfMemory && hipGetDevice(&device) == hipSuccess && return_scratch(device)) e = hipMalloc(p, bytes);
+    if (e != hipSuccess) *p = nullptr;
+    return e;
+}
+
 hipError_t scratch_alloc(void** p, size_t bytes, hipStream_t st)
 {
     *p = nullptr;
@@ -354,6 +381,7 @@ hipError_t scratch_alloc(void** p, size_t bytes, hipStream_t st)
         m = g_scratch[device];
     }
     if (e == hipSuccess) e = m ? hipMallocFromPoolAsync(p, bytes, m, st) : hipMallocAsync(p, bytes, st);
+    if (e == hipErrorOutOfMemory && m && return_scratch(device)) e = hipMallocFromPoolAsync(p, bytes, m, st);
     if (e != hipSuccess) *p = nullptr;
     return e;
 }

@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
-OUT_OF_MEMORY, UNKNOWN = 2, 999  # hipErrorOutOfMemory, hipErrorUnknown
+OUT_OF_MEMORY, CAPTURE_UNSUPPORTED, UNKNOWN = 2, 900, 999  # hipError_t
 
 
 def build(folder):

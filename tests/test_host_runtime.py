@@ -42,3 +42,41 @@ assert d.value == 1
 print("ok")
 """)
     assert out.strip() == "ok"
+
+
+def test_creation_takes_kept_scratch_back(so):
+    """Scratch kept between calls is given back before an allocation is
+    reported as failed: a lattice, a c2 field, a pool's slots, a larger scratch."""
+    out = fake_gpu.run(so, """
+MB = 1 << 20
+L = lbm.Lattice(700, 900, 0.7, 0.3, "f64")
+L.init(None, None, None)
+big = lbm.Lattice(900, 1000, 0.7, 0.3, "f64")
+big.init(None, None, None)
+
+def tight(free):  # 45 MB of scratch kept, `free` left beside it
+    fake.fake_limit(0, 1 << 40)
+    L.get_f()
+    fake.fake_limit(0, fake.fake_used(0) + free)
+
+tight(10 * MB)
+lbm.Lattice(500, 900, 0.7, 0.3, "f32").close()  # 34 MB
+tight(1 * MB)
+L.set_c2_field(np.full((900, 700), 0.3))  # the field itself takes 5 MB, its staging as much
+fake.fake_limit(0, 1 << 40)
+P = lbm.Pool(1 << 30, "f32")
+tight(10 * MB)
+P = lbm.Pool(40 * MB, "f32")
+P.add(400, 900, 0.7, 0.3)  # the pool's chunk is its budget
+tight(30 * MB)
+big.get_f()  # 65 MB
+for f, need in ((lambda: lbm.Lattice(2000, 2000, 0.7, 0.3, "f64"), 576 * MB),):  # what does not fit is still refused
+    tight(10 * MB)
+    try:
+        f()
+        raise SystemExit("accepted")
+    except lbm.LBMError as e:
+        assert e.status == lbm.ENOMEM
+print("ok")
+""")
+    assert out.strip() == "ok"
