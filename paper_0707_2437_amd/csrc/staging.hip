@@ -403,7 +403,9 @@ hipError_t copy_out(const HostPart* part, int nparts, hipStream_t st)
     hipError_t e = hipSuccess;
     for (int k = 0; k < nparts && e == hipSuccess; ++k)
         if (part[k].dst) e = hipMemcpyAsync(part[k].dst, part[k].src, part[k].bytes, hipMemcpyDeviceToHost, st);
-    return e == hipSuccess ? hipStreamSynchronize(st) : e;
+    // also after a failure: no copy of an earlier part may outlive the call
+    const hipError_t es = hipStreamSynchronize(st);
+    return e == hipSuccess ? es : e;
 }
 
 }  // namespace lbm

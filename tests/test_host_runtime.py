@@ -80,3 +80,22 @@ for f, need in ((lambda: lbm.Lattice(2000, 2000, 0.7, 0.3, "f64"), 576 * MB),): 
 print("ok")
 """)
     assert out.strip() == "ok"
+
+
+def test_failed_read_leaves_no_copy_behind(so):
+    """A read that fails half way has no copy under way into the caller's arrays."""
+    out = fake_gpu.run(so, """
+import ctypes
+L = lbm.Lattice(70, 90, 0.7, 0.3, "f64")
+L.init(None, None, None)
+a, b = ctypes.c_void_p(), ctypes.c_void_p()
+for p in (a, b):
+    assert fake.hipHostMalloc(ctypes.byref(p), 70 * 90 * 8, 0) == 0
+st = L._L.lbm_get_stream(L._h)
+fake.fake_fail(b"hipMemcpyAsync", 1, fake_gpu.UNKNOWN)
+assert L._L.lbm_moments(L._h, a, b, None, None) == lbm.EDEVICE
+assert fake.fake_pending(st) == 0
+assert L._L.lbm_moments(L._h, a, b, None, None) == lbm.OK
+print("ok")
+""")
+    assert out.strip() == "ok"
