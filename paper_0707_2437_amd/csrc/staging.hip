@@ -214,13 +214,9 @@ struct Shared {
     }
 };
 
-hipError_t staged(const Plan& plan, hipStream_t st)
+hipError_t staged(const Plan& plan, RingLease& lease, hipStream_t st)
 {
-    RingLease lease;
-    int device = 0;
-    hipError_t e = stream_device(st, &device);
-    if (e == hipSuccess) e = lease.take(device);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
     Shared sh(plan, lease.r.p);
     int sent = 0;
     // starts the DMA of every chunk whose slot is free
@@ -396,8 +392,13 @@ hipError_t copy_out(const HostPart* part, int nparts, hipStream_t st)
         if (direct(part[k].dst)) stage = false;
     }
     if (stage && bytes >= kStageFrom) {
-        const hipError_t e = staged(Plan(part, nparts), st);
-        if (e != hipErrorOutOfMemory) return e;  // no pinned memory left: as small copies go
+        RingLease lease;
+        int device = 0;
+        hipError_t e = stream_device(st, &device);
+        if (e == hipSuccess) e = lease.take(device);
+        if (e == hipSuccess && (e = staged(Plan(part, nparts), lease, st)) != hipErrorOutOfMemory) return e;
+        // no pinned memory left, or none to be had while another thread
+        // captures a graph: as small copies go
         (void)hipGetLastError();
     }
     hipError_t e = hipSuccess;

@@ -99,3 +99,21 @@ assert L._L.lbm_moments(L._h, a, b, None, None) == lbm.OK
 print("ok")
 """)
     assert out.strip() == "ok"
+
+
+@pytest.mark.parametrize("call,after", [("hipHostMalloc", 0), ("hipEventCreateWithFlags", 0),
+                                        ("hipEventCreateWithFlags", 5)])
+@pytest.mark.parametrize("error", [fake_gpu.OUT_OF_MEMORY, fake_gpu.CAPTURE_UNSUPPORTED])
+def test_read_without_a_staging_ring(so, call, after, error):
+    """Where no ring can be made (no pinned memory; another thread captures a
+    graph) a large read goes as a small one does."""
+    out = fake_gpu.run(so, f"""
+L = lbm.Lattice(700, 900, 0.7, 0.3, "f64")
+L.init(None, None, None)
+fake.fake_fail(b"{call}", {after}, {error})
+f = L.get_f()
+assert not f.any()
+assert fake.fake_pending(L._L.lbm_get_stream(L._h)) == 0
+print("ok")
+""")
+    assert out.strip() == "ok"
