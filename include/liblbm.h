@@ -199,7 +199,7 @@ size_t lbm_footprint_bytes(int nx, int ny, int dtype);
  * LBM_TILE_* bits. March form: nw = 64-lane waves per workgroup (1 or 4),
  * each owning its own column strip of 64 * vx sites and marching h >= 1
  * rows. Vertical-stack form (LBM_TILE_VSTACK): nw = 4, 8 or 16 waves per
- * workgroup covering one strip and nw - 2 rows (h is ignored). Default:
+ * workgroup covering one strip and nw - 2 rows (h is not used). Default:
  * the two-step form below; nw = 16 and non-temporal stores with vx = 1 for
  * LBM_F64 and vx = 2 for LBM_F32 and LBM_F32S; vx = 1, nw = 32 and plain
  * stores for LBM_F16S. Results do not depend on the shape (bitwise). LBM_EINVAL for an unsupported shape, for
@@ -216,7 +216,8 @@ size_t lbm_footprint_bytes(int nx, int ny, int dtype);
  * step while inlet/outlet boundaries are set, use the single-step vertical
  * stack (vx = 2, nw = 8, non-temporal stores), the passes below aside. The
  * results are those of single steps, bit for bit (c2 fields included).
- * With the dtype's default shape, lattices large enough (from about 600^2
+ * With the dtype's default shape as lbm_get_tile reports it (h = 8; with any
+ * other h the pairs are all it takes), lattices large enough (from about 600^2
  * sites) that fit the row-interleaved layout advance four or eight steps per
  * launch instead (the cascade kernel); the pairs take what is left of a count.
  * Small lattices (at most 16 rows, or up to about 250^2 sites) advance up to

@@ -132,7 +132,8 @@ StepTile make_tile(const lbm_lattice* L)
 }
 
 // The next launch of a lattice with n steps to take: the steps it takes and
-// the kernel. The default shape takes, where they are faster, block passes
+// the kernel. The default shape, its h included (which the two-step kernel does
+// not use: with any other it runs alone), takes, where they are faster, block passes
 // (small lattices) or cascade passes (large ones, whose buffer is within
 // reach of 32-bit offsets: the row-interleaved layout); a two-step shape
 // takes pairs; a lone last step, and the steps of a lattice with inlet/outlet
@@ -149,7 +150,7 @@ Pass next_pass(const lbm_lattice* L, int n)
 {
     const bool inlet = L->xbc == LBM_XBC_INLET_OUTLET;
     const TileDefault td = default_tile(L->dtype);
-    if (L->vx == td.vx && L->nw == td.nw && L->kflags == td.flags) {
+    if (L->vx == td.vx && L->nw == td.nw && L->h == td.h && L->kflags == td.flags) {
         if (!(inlet && L->field)) {
             const BlockShape b = block_shape(L->dtype, L->nx, L->ny, n, inlet);
             if (b.ns) return {Pass::kBlock, b.ns, b};

@@ -121,8 +121,10 @@ void __hipRegisterFunction(void**, const void* host, char*, const char* name, un
 {
     Hold hold(g_mu);
     int st = 0;
-    char* d = abi::__cxa_demangle(name, nullptr, nullptr, &st);
-    std::string s = d ? d : name;
+    std::string s = name;
+    for (size_t i; (i = s.find("DF16_")) != std::string::npos;) s.replace(i, 5, "Dh");  // _Float16, as the demangler knows it
+    char* d = abi::__cxa_demangle(s.c_str(), nullptr, nullptr, &st);
+    if (d) s = d;
     std::free(d);
     if (s.rfind("void ", 0) == 0) s = s.substr(5);
     size_t i = 0;

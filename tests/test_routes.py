@@ -1,0 +1,42 @@
+"""Which kernels lbm_step launches, read off the library's own launches over
+a stand-in HIP runtime (fake_hip.cpp)."""
+import pytest
+
+import fake_gpu
+
+DEFAULT = {"f64": (1, 16, 16 | 32 | 2), "f32": (2, 16, 16 | 32 | 2), "f32s": (2, 16, 16 | 32 | 2), "f16s": (1, 32, 16 | 32)}
+
+
+@pytest.fixture(scope="module")
+def so(tmp_path_factory):
+    lib = fake_gpu.build(str(tmp_path_factory.mktemp("fake")))
+    if lib is None:
+        pytest.skip("g++ not found")
+    return lib
+
+
+def case(nx, ny, dtype, *calls, **kw):
+    return dict({"nx": nx, "ny": ny, "dtype": dtype, "calls": calls}, **kw)
+
+
+@pytest.mark.parametrize("dtype", DEFAULT)
+def test_a_shape_given_without_the_defaults_h_is_that_kernel_alone(so, dtype):
+    """The default two-step shape as lbm_get_tile reports it takes block and
+    cascade passes, as a new lattice does; with any other h it takes pairs
+    only, so that the two-step kernel can be had (and tested) by itself."""
+    vx, nw, flags = DEFAULT[dtype]
+    sizes = [(64, 64), (4000, 4), (2400, 2400)]
+    new, own, pairs, field = (
+        [case(nx, ny, dtype, 9, **kw) for nx, ny in sizes]
+        for kw in ({}, {"tile": "own"}, {"tile": (vx, nw, 0, flags)}, {"tile": (vx, nw, 0, flags), "field": True}))
+    got = fake_gpu.routes(so, new + own + pairs + field)
+    assert got[:3] == got[3:6]
+    assert set(got[0]) == {"block", "step"} and set(got[1]) == {"block"}
+    assert got[2][0] in ("cascade8", "cascade4")
+    assert all(r == ["pair"] * 4 + ["step"] for r in got[6:])
+
+
+def test_the_environments_shape_follows_the_same_rule(so):
+    c = [case(64, 64, "f32", 8)]
+    assert fake_gpu.routes(so, c, {"LBM_TILE": "2,16,0,50"}) == [["pair"] * 4]
+    assert fake_gpu.routes(so, c, {"LBM_TILE": "2,16,8,50"}) == [["block"] * 2]
