@@ -40,3 +40,23 @@ def test_the_environments_shape_follows_the_same_rule(so):
     c = [case(64, 64, "f32", 8)]
     assert fake_gpu.routes(so, c, {"LBM_TILE": "2,16,0,50"}) == [["pair"] * 4]
     assert fake_gpu.routes(so, c, {"LBM_TILE": "2,16,8,50"}) == [["block"] * 2]
+
+
+def test_the_cascade_sizes_take_cascade_passes(so):
+    import cascade_sizes
+    cases = list(cascade_sizes.cases())
+    got = fake_gpu.routes(so, [case(nx, ny, dtype, steps, steps + 5, **kw) for dtype, steps, nx, ny, _, kw in cases])
+    for (dtype, steps, nx, ny, name, _), r in zip(cases, got):
+        r = [k for k in r if k != "ghosts"]  # FP16: after each call's passes
+        tail = ["step"] + (["xbc"] if name == "inlet" else [])
+        first = "cascade%d" % steps
+        assert r[0] == first and r[1] == first, (dtype, steps, nx, ny, name, r)
+        assert r[2:] == ["cascade4"] + tail, (dtype, steps, nx, ny, name, r)
+
+
+def test_the_two_step_sizes_take_pairs(so):
+    import cascade_sizes
+    cases = list(cascade_sizes.pair_cases())
+    got = fake_gpu.routes(so, [case(nx, ny, dtype, 7, **kw) for dtype, nx, ny, kw in cases])
+    for c, r in zip(cases, got):
+        assert r == ["pair"] * 3 + ["step"], (c, r)
