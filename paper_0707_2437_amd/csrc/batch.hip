@@ -32,7 +32,7 @@ __device__ __forceinline__ bool batch_item(const BatchLat* __restrict__ lats, co
     const void* src = odd ? L.tile.dst : L.tile.src;
     void* dst = odd ? const_cast<void*>(L.tile.src) : L.tile.dst;
     const int t0 = (i - L.item_begin) * L.per_item;
-    const int t1 = min(t0 + L.per_item, L.ntiles);
+    const int t1 = min(t0 + L.per_item, L.tile.nstrips * L.tile.nchunks);
     for (int t = t0; t < t1; ++t) {
         if (t > t0) __syncthreads();  // lds of the previous tile is still being read
         // pools step the paper's model: centred on the weights (see Centre)
@@ -74,7 +74,7 @@ __device__ __forceinline__ Unit find_unit(const BatchLat* __restrict__ lats, con
         if (s < ldc(&L->nsteps)) {
             const int per = ldc(&L->per_item);
             const int t0 = (i - ldc(&L->item_begin)) * per;
-            return Unit{L, i, t0, min(t0 + per, ldc(&L->ntiles))};
+            return Unit{L, i, t0, min(t0 + per, ldc(&L->tile.nstrips) * ldc(&L->tile.nchunks))};
         }
     }
     return Unit{nullptr, i, 0, 0};
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
             }
             const int per = ldc(&L->per_item);
             const int t0 = (i - ldc(&L->item_begin)) * per;
-            const int t1 = min(t0 + per, ldc(&L->ntiles));
+            const int t1 = min(t0 + per, ldc(&L->tile.nstrips) * ldc(&L->tile.nchunks));
             for (int t = t0; t < t1; ++t) {
                 const bool last = t + 1 == t1;
                 const int strip = t % a.nstrips;

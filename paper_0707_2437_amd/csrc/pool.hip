@@ -254,10 +254,10 @@ hipError_t ensure_cap(lbm_pool* P, int n, int nitems)
 // Append lattice descriptor b (tile already set) and its work items.
 void add_lattice(lbm_pool* P, BatchLat b)
 {
-    b.ntiles = b.tile.nstrips * b.tile.nchunks;
+    const int ntiles = b.tile.nstrips * b.tile.nchunks;
     b.per_item = P->per_item;
     b.item_begin = (int)P->h_items.size();
-    const int nitems = (b.ntiles + b.per_item - 1) / b.per_item;
+    const int nitems = (ntiles + b.per_item - 1) / b.per_item;
     const int l = (int)P->h_lats.size();
     for (int k = 0; k < nitems; ++k) P->h_items.push_back(l);
     P->h_lats.push_back(b);
@@ -380,13 +380,13 @@ void add_cascade(lbm_pool* P, const Slot& S, const CascadeShape& c, int passes, 
     b.tile.h = ((S.ny + chunks - 1) / chunks + 1) / 4 * 4 + 2;
     b.tile.nstrips = (S.nx + w - 1) / w;
     b.tile.nchunks = (S.ny + b.tile.h - 1) / b.tile.h;
-    b.t0 = buffer_t0;
+    b.t0 = (int)(buffer_t0 & 1);
     b.nsteps = passes;
-    b.ntiles = b.tile.nstrips * b.tile.nchunks;
+    const int ntiles = b.tile.nstrips * b.tile.nchunks;
     b.per_item = 1;
     b.item_begin = (int)P->h_items.size() - P->deep_items_at;
     const int l = (int)P->h_lats.size() - P->deep_lats_at;
-    for (int k = 0; k < b.ntiles; ++k) P->h_items.push_back(l);
+    for (int k = 0; k < ntiles; ++k) P->h_items.push_back(l);
     P->h_lats.push_back(b);
     P->deep_passes = std::max(P->deep_passes, passes);
 }
@@ -482,7 +482,7 @@ int lbm_pool_add(lbm_pool* P, int nx, int ny, double tau, double c2)
     S.tau = tau;
     S.c2 = c2;
     S.g = g;
-    S.coef = make_coef(tau, c2, LBM_MODEL_FORCING);
+    S.coef = make_coef(P->dtype, tau, c2, LBM_MODEL_FORCING);
     S.bytes = bytes;
     const size_t fb = footprint(g, P->esize);
     S.span = bytes;
@@ -581,7 +581,7 @@ static int build_batch(lbm_pool* P, const int* slots, const int* nsteps, int cou
         const Slot& S = P->slots[slots[k]];
         BatchLat b{};
         b.tile = slot_tile(S, P->vx, P->nw, P->two);
-        b.t0 = buffer_time(S);
+        b.t0 = (int)(buffer_time(S) & 1);
         b.nsteps = n;
         add_lattice(P, b);
         *nmax = std::max(*nmax, n);
@@ -872,7 +872,7 @@ int lbm_pool_autotune(lbm_pool* P, const int* slots, int count, int reps, int us
             }
             BatchLat b{};
             b.tile = slot_tile(P->slots[slots[j]], k.vx, k.nw, two);
-            b.t0 = buffer_time(P->slots[slots[j]]);
+            b.t0 = (int)(buffer_time(P->slots[slots[j]]) & 1);
             b.nsteps = two ? 2 : 1;
             add_lattice(P, b);
         }

@@ -417,13 +417,18 @@ __device__ __forceinline__ void collide_col(const V& v, C drho, C gx, C gy, cons
     const C ux = jx * ir, uy = jy * ir;
     const C tx = jx * ux, ty = jy * uy, txy = jx * uy;
     const C s = tx + ty;
-    auto even = [&](C a, C b, C z) {
-        if constexpr (RC || sizeof(C) == sizeof(float)) return fmac(a, drho, b * s);
-        else return fmac(a, drho, fmac(b, s, z));
-    };
-    const C pa = even(k.a1, k.b1, k.z1), pd = even(k.a2, k.b2, k.z2);
+    C p0, pa, pd;
+    if constexpr (RC || sizeof(C) == sizeof(float)) {
+        p0 = fmac(k.a0, drho, k.b0 * s);
+        pa = fmac(k.a1, drho, k.b1 * s);
+        pd = fmac(k.a2, drho, k.b2 * s);
+    } else {
+        p0 = fmac(k.a0, drho, fmac(k.b0, s, k.z0));
+        pa = fmac(k.a1, drho, fmac(k.b1, s, k.z1));
+        pd = fmac(k.a2, drho, fmac(k.b2, s, k.z2));
+    }
     const C q1 = fmac(k.as1, gx, k.w3 * jx), q2 = fmac(k.as1, gy, k.w3 * jy);
-    o[0] = v.fma(k.om1, 0, even(k.a0, k.b0, k.z0));
+    o[0] = v.fma(k.om1, 0, p0);
     const C p1 = fmac(k.t45, tx, pa), p2 = fmac(k.t45, ty, pa);
     o[1] = v.fma(k.om1, 1, p1 + q1);
     o[3] = v.fma(k.om1, 3, p1 - q1);

@@ -501,7 +501,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
     const void* src = odd ? L.tile.dst : L.tile.src;
     void* dst = odd ? const_cast<void*>(L.tile.src) : L.tile.dst;
     const int t0 = (i - L.item_begin) * L.per_item;
-    const int t1 = min(t0 + L.per_item, L.ntiles);
+    const int t1 = min(t0 + L.per_item, L.tile.nstrips * L.tile.nchunks);
     for (int t = t0; t < t1; ++t) {
         if (t > t0) __syncthreads();  // lds of the previous tile is still being read
         step2_tile<T, SHIFT, VX, NW, NTS, false, false>(L.tile, src, dst, t % L.tile.nstrips, t / L.tile.nstrips,
@@ -550,7 +550,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
             void* dst = odd ? const_cast<void*>(a.src) : a.dst;
             const int per = ldc(&L->per_item);
             const int t0 = (i - ldc(&L->item_begin)) * per;
-            const int t1 = min(t0 + per, ldc(&L->ntiles));
+            const int t1 = min(t0 + per, ldc(&L->tile.nstrips) * ldc(&L->tile.nchunks));
             for (int t = t0; t < t1; ++t) {
                 if (t > t0) __syncthreads();  // lds of the previous tile is still being read
                 step2_tile<T, SHIFT, VX, NW, NTS, false, false, 1>(a, src, dst, t % a.nstrips, t / a.nstrips,
