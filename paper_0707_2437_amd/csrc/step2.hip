@@ -157,7 +157,11 @@ __device__ __forceinline__ void step2_tile(const StepTile& a, const void* src, v
 
     const Geom g = a.g;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int lane = threadIdx.x & 63;
+    // Opaque: a batched kernel's loop over tiles would hold what is derived from
+    // it in registers throughout, one too many in FP32-shifted pools (whose
+    // spill cost 8 % of a pass).
+    int lane = threadIdx.x & 63;
+    asm("" : "+v"(lane));
     const int y0 = grp * R2;
     const int nrows = min(R2, g.ny - y0);
     const int y = y0 - 3 + wave;
