@@ -236,13 +236,15 @@ int lbm_set_tile(lbm_lattice* L, int vx, int nw, int h, int flags);
 int lbm_get_tile(const lbm_lattice* L, int* vx, int* nw, int* h, int* flags);
 
 /* Autotuner: time the candidate kernel shapes on this lattice, single- and
- * two-step and the default shape's four-step passes, each over four steps
- * (reps timed rounds each, after warm-up
+ * two-step and the default shape's longer passes, each over eight steps with
+ * the lattice's boundaries (reps timed rounds each, after warm-up
  * launches; every launch reads the current state and writes the spare
- * buffer, so the state is unchanged) and apply the fastest. With use_cache != 0 a shape found before for the same GPU
- * architecture, dtype and nx x ny is applied without timing. Results are
- * remembered for the process and, if the environment variable LBM_TUNE_CACHE
- * names a file, appended to it (one JSON object per line). Synchronous.
+ * buffer, so the state is unchanged) and apply the fastest. With use_cache != 0
+ * a shape found before for the same GPU architecture, dtype and nx x ny, with
+ * or without a c2 field and inlet/outlet boundaries, is applied without timing.
+ * Results are remembered for the process and, if the environment variable
+ * LBM_TUNE_CACHE names a file, appended to it (one JSON object per line; lines
+ * of a library whose shapes stood for other launches are not used). Synchronous.
  * LBM_ESTATE before init. */
 int lbm_autotune(lbm_lattice* L, int reps, int use_cache);
 

@@ -792,7 +792,7 @@ int lbm_pool_autotune(lbm_pool* P, const int* slots, int count, int reps, int us
     // the persistent kernel is tuned on its own launches (its best shape differs)
     const bool pers = P->mode == LBM_POOL_PERSISTENT;
     char key[160];
-    std::snprintf(key, sizeof(key), "%s|%s|%d|n2^%d|s2^%d", device_arch().c_str(), pers ? "pool-persistent" : "pool",
+    std::snprintf(key, sizeof(key), "%s|%s|%d|n2^%d|s2^%d", tune_key_head().c_str(), pers ? "pool-persistent" : "pool",
                   P->dtype, lc, ls);
     TileCand c{};
     if (use_cache && tune_cache_get(key, &c)) {

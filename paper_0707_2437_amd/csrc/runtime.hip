@@ -379,8 +379,10 @@ int lbm_autotune(lbm_lattice* L, int reps, int use_cache)
     if (!L || reps < 1) return LBM_EINVAL;
     if (!L->ready) return LBM_ESTATE;
     char key[160];
-    std::snprintf(key, sizeof(key), "%s|%s|%d|%dx%d", device_arch().c_str(), L->field ? "lattice-field" : "lattice",
-                  L->dtype, L->nx, L->ny);
+    // boundaries decide which passes a shape can take
+    const bool inlet = L->xbc == LBM_XBC_INLET_OUTLET;
+    std::snprintf(key, sizeof(key), "%s|lattice%s%s|%d|%dx%d", tune_key_head().c_str(), L->field ? "-field" : "",
+                  inlet ? "-inlet" : "", L->dtype, L->nx, L->ny);
     TileCand c{};
     if (use_cache && tune_cache_get(key, &c)) return lbm_set_tile(L, c.vx, c.nw, c.h, c.flags);
     std::vector<TileCand> cands = lattice_candidates(L->dtype);
@@ -388,16 +390,14 @@ int lbm_autotune(lbm_lattice* L, int reps, int use_cache)
         cands.erase(std::remove_if(cands.begin(), cands.end(),
                                    [](const TileCand& k) { return !(k.flags & LBM_TILE_VSTACK); }),
                     cands.end());
-    // Each candidate is timed over eight steps, as lbm_step would launch them
-    // (the inlet aside), reading cur and writing nxt with no swap: the state
-    // does not change.
+    // Each candidate is timed over eight steps, as lbm_step would launch them,
+    // reading cur and writing nxt with no swap: the state does not change.
     auto launch = [&](const TileCand& k) -> hipError_t {
         lbm_lattice tmp = *L;
         tmp.vx = k.vx;
         tmp.nw = k.nw;
         tmp.h = k.h;
         tmp.kflags = k.flags;
-        tmp.xbc = LBM_XBC_PERIODIC;
         hipError_t e = hipSuccess;
         for (int n = 8; n > 0 && e == hipSuccess;) {
             const Pass p = next_pass(&tmp, n);

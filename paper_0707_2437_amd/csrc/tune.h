@@ -16,7 +16,11 @@ struct TileCand {
     int vx, nw, h, flags, ch;
 };
 
-std::string device_arch();
+// The first part of a record's key: the GPU architecture, and a revision that is
+// raised when the launches that a shape stands for change, so that records of
+// earlier launches (in a file) are timed again. 2: the default shapes stand for
+// block and cascade passes.
+std::string tune_key_head();
 bool tune_cache_get(const std::string& key, TileCand* out);
 void tune_cache_put(const std::string& key, const TileCand& c, float us);
 std::vector<TileCand> lattice_candidates(int dtype);

@@ -3,8 +3,8 @@
 // Every candidate shape is timed on the caller's own lattice(s) with launches
 // that read the current buffer and write the other one without swapping them,
 // so tuning never changes the state (and results do not depend on the shape
-// anyway). The fastest shape is applied and remembered per (GPU architecture,
-// form, dtype, size): in memory for the process, and, when the environment
+// anyway). The fastest shape is applied and remembered per (GPU architecture and
+// revision, form, dtype, size): in memory for the process, and, when the environment
 // variable LBM_TUNE_CACHE names a file, in that file as one JSON object per
 // line (later lines override earlier ones).
 #include <hip/hip_runtime.h>
@@ -53,7 +53,7 @@ void load_cache_locked()
 
 }  // namespace
 
-std::string device_arch()
+static std::string device_arch()
 {
     int dev = 0;
     hipDeviceProp_t prop;
@@ -62,6 +62,8 @@ std::string device_arch()
     const size_t colon = a.find(':');
     return colon == std::string::npos ? a : a.substr(0, colon);
 }
+
+std::string tune_key_head() { return device_arch() + "/2"; }
 
 bool tune_cache_get(const std::string& key, TileCand* out)
 {

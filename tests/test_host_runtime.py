@@ -117,3 +117,47 @@ assert fake.fake_pending(L._L.lbm_get_stream(L._h)) == 0
 print("ok")
 """)
     assert out.strip() == "ok"
+
+
+def test_tuned_shapes_of_earlier_launches_are_timed_again(so, tmp_path):
+    """A tune record whose key lacks the revision (written when the default
+    shape stood for two-step launches) is not applied."""
+    import json
+    cache = tmp_path / "tune.jsonl"
+    old = [("gfx950|lattice|1|1000x777", 4, 16, 8, 16), ("gfx950|pool|1|n2^1|s2^21", 4, 8, 2, 2)]
+    cache.write_text("".join(json.dumps({"key": k, "vx": vx, "nw": nw, "h": h, "flags": f, "ch": 8, "us": 1.0}) + "\n"
+                             for k, vx, nw, h, f in old))
+    out = fake_gpu.run(so, """
+fake.fake_fast(b"cascade_kernel")
+with lbm.Lattice(1000, 777, 0.7, 0.3, "f32") as L:
+    L.init_device(None, None, None)
+    print(L.autotune(reps=1, use_cache=True) == L.get_tile() == (2, 16, 8, 50))
+P = lbm.Pool(1 << 30, "f32")
+s = [P.add(1000, 777, 0.7, 0.3) for _ in range(2)]
+for k in s: P.init_device(k, None, None, None)
+print(P.autotune(s, reps=1, use_cache=True) == (2, 16, 34))
+""", {"LBM_TUNE_CACHE": str(cache)})
+    assert out.split() == ["True", "True"]
+    assert len(cache.read_text().splitlines()) == 4  # both were timed and recorded
+
+
+def test_tuning_knows_the_boundaries(so):
+    """A lattice with inlet/outlet boundaries is tuned on the launches it makes:
+    the default's passes, against single steps and a boundary launch each, and not
+    by a record of a periodic lattice."""
+    out = fake_gpu.run(so, """
+L = lbm.Lattice(350, 350, 0.7, 0.3, "f32")
+L.init_device(None, None, None)
+fake.fake_fast(b"step2_vstack_kernel<float, false, 1, 12")
+print(L.autotune(reps=1, use_cache=True)[:2] == (1, 12))
+L.set_x_boundaries(lbm.XBC_INLET_OUTLET, 1e-3, 500.0)
+fake.fake_log()
+fake.fake_fast(b"block_kernel")
+print(L.autotune(reps=1, use_cache=True) == (2, 16, 8, 50))
+log = fake.fake_log().decode()
+print("xbc_kernel" in log and "step2_vstack" not in log)
+L.set_x_boundaries(lbm.XBC_PERIODIC)
+fake.fake_log()
+print(L.autotune(reps=1, use_cache=True)[:2] == (1, 12) and not fake.fake_log())  # its own record
+""")
+    assert out.split() == ["True"] * 4
