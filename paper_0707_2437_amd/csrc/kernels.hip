@@ -360,11 +360,12 @@ __device__ inline void reduce_partials(const double* __restrict__ partials, int 
 // the lattice size, and the last workgroup to finish sums the blocks'
 // partials in a fixed order: the totals are deterministic. `done` counts
 // finished workgroups; it is zero between launches.
+// NARROW (one column per lane): a wave takes several rows, 2^nseg lanes each.
 // One call with its wait, against one element per thread, a 64-bit division
 // per site, a second launch for the sums and a copy of the totals: FP32
 // 4096^2 with fields 459 to 220 us (4.6 TB/s), FP64 482 to 341, FP16 8192^2
 // 1693 to 656, 397 x 131 FP32 30.0 to 20.7.
-template <class T, bool SHIFT, int V>
+template <class T, bool SHIFT, int V, bool NARROW>
 __global__ __launch_bounds__(kRedThreads) void moments_kernel(const T* __restrict__ s, Geom g, int nseg,
                                                               double* __restrict__ rho, double* __restrict__ ux,
                                                               double* __restrict__ uy, double* __restrict__ partials,
@@ -377,17 +378,18 @@ __global__ __launch_bounds__(kRedThreads) void moments_kernel(const T* __restric
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const char* pb[9];
     src_bases<T>(s, g, pb);
-    const int nunits = nseg * g.ny;
+    const int rows = NARROW ? 64 >> nseg : 1;  // of a unit
+    const int nunits = NARROW ? (g.ny + rows - 1) / rows : nseg * g.ny;
     double dr = 0.0, jx = 0.0, jy = 0.0;
     for (int u = (int)blockIdx.x * kRedWaves + wave; u < nunits; u += (int)gridDim.x * kRedWaves) {
-        const int y = u / nseg;
-        const int x = (u - y * nseg) * (64 * V) + lane * V;
-        const int nv = min(V, g.nx - x);
+        const int y = NARROW ? u * rows + (lane >> nseg) : u / nseg;
+        const int x = NARROW ? lane & ((1 << nseg) - 1) : (u - y * nseg) * (64 * V) + lane * V;
+        const int nv = NARROW && y >= g.ny ? 0 : min(V, g.nx - x);
         if (nv <= 0) continue;
         const char* rb[9];
         row_bases<T>(pb, g, y, rb);
         T v[9][V];
-        if (nv == V && x >= 1 && x + V < g.nx) {
+        if (!NARROW && nv == V && x >= 1 && x + V < g.nx) {
             constexpr int A = es < 4 ? (int)es : 4;
 #pragma unroll
             for (int i = 0; i < 9; ++i) {
@@ -681,19 +683,30 @@ int moments_blocks(const Geom& g)
     return (int)(nb < 1024 ? nb : 1024);
 }
 
-// Columns per lane of the moments kernel: 16 bytes of a plane, at most 4.
+// Columns per lane of the moments kernel: 16 bytes of a plane, at most 4. Up
+// to 64 columns a wave takes several rows: with a segment each, most of its lanes
+// idle. Totals and fields in us, segments / rows (before: one site per thread):
+// 4 x 262144 FP32 260 / 76 (90), FP64 227 / 76 (90); 16 x 65536 FP32 91 / 40 (49);
+// 64 x 16384 FP32 41 / 37 (49), FP64 42 / 40 (50).
 hipError_t launch_moments(int dtype, const void* s, const Geom& g, double* rho, double* ux, double* uy,
                           double* partials, unsigned* done, double* totals, hipStream_t st)
 {
+    const bool narrow = g.nx <= 64;
     const int v = dtype == 0 ? 2 : 4;
-    const int nseg = (g.nx + 64 * v - 1) / (64 * v);
-    const long long units = (long long)nseg * g.ny;
+    int nseg = (g.nx + 64 * v - 1) / (64 * v);
+    if (narrow)
+        for (nseg = 2; (1 << nseg) < g.nx;) ++nseg;
+    const long long units = narrow ? ((long long)g.ny + (64 >> nseg) - 1) / (64 >> nseg) : (long long)nseg * g.ny;
     if (units > 0x7fffffffLL - 4096) return hipErrorInvalidConfiguration;
     const long long want = (units + kRedWaves - 1) / kRedWaves;
     const int nb = want < moments_blocks(g) ? (int)want : moments_blocks(g);
     LBM_DISPATCH(dtype, {
-        hipLaunchKernelGGL((moments_kernel<T, S, sizeof(T) == 8 ? 2 : 4>), dim3(nb), dim3(kRedThreads), 0, st,
-                           (const T*)s, g, nseg, rho, ux, uy, partials, done, totals);
+        if (narrow)
+            hipLaunchKernelGGL((moments_kernel<T, S, 1, true>), dim3(nb), dim3(kRedThreads), 0, st, (const T*)s, g, nseg, rho,
+                               ux, uy, partials, done, totals);
+        else
+            hipLaunchKernelGGL((moments_kernel<T, S, sizeof(T) == 8 ? 2 : 4, false>), dim3(nb), dim3(kRedThreads), 0, st,
+                               (const T*)s, g, nseg, rho, ux, uy, partials, done, totals);
         return hipGetLastError();
     })
 }
