@@ -178,7 +178,9 @@ hipError_t launch_block(int dtype, const BlockShape& b, const StepTile& t, const
 // 3.25). With inlet/outlet boundaries the alternative is a cascade pass: 3
 // steps up to 800 tiles in FP64 (400^2 5.5 us per step, cascade 6.3; 512^2 7.3
 // and 7.1), 1250 in FP32 (600^2 5.6 and 5.8; 700^2 7.0 and 5.8), 2500 in FP16
-// (1000 x 777 10.5 and 12.3).
+// (1000 x 777 10.5 and 12.3). One step alone could also be a single-step launch and one
+// for the boundaries, which in FP16 is as fast from 1500 tiles (650^2 10.1 and 10.6;
+// 700^2 11.2 and 10.2; 5000 x 100 10.8 and 10.0).
 BlockShape block_shape(int dtype, int nx, int ny, int n, bool inlet)
 {
     BlockShape best;
@@ -209,7 +211,7 @@ BlockShape block_shape(int dtype, int nx, int ny, int n, bool inlet)
     b.ns = 4;
     if (b.tiles(nx, ny) > 256) {
         b.ns = 3;
-        static const int most[4] = {800, 1250, 1250, 2500};
+        const int most[4] = {800, 1250, 1250, n == 1 ? 1500 : 2500};
         if (b.tiles(nx, ny) > (inlet ? most[dtype] : (dtype == 0 ? 128 : 256))) return best;
     }
     if (b.ns > n) b.ns = n;

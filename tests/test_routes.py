@@ -60,3 +60,12 @@ def test_the_two_step_sizes_take_pairs(so):
     got = fake_gpu.routes(so, [case(nx, ny, dtype, 7, **kw) for dtype, nx, ny, kw in cases])
     for c, r in zip(cases, got):
         assert r == ["pair"] * 3 + ["step"], (c, r)
+
+
+def test_one_fp16_step_with_an_inlet_takes_the_faster_launches(so):
+    """Where a single-step launch and one for the boundaries are faster than a block
+    pass of one step (from 1500 tiles), a lone step takes them."""
+    inlet = {"inlet": (0.01, 50.0)}
+    got = fake_gpu.routes(so, [case(nx, ny, "f16s", n, **inlet)
+                               for nx, ny in ((650, 650), (700, 700), (5000, 100)) for n in (1, 2)])
+    assert got == [["block"], ["block"], ["step", "xbc"], ["block"], ["step", "xbc"], ["block"]]
