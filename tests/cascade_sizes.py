@@ -37,3 +37,12 @@ def pair_cases():
         for nx, ny in PAIR_SIZES + ([(1103, 1021)] if dtype == "f16s" else []):
             for name in ("plain", "equilibrium", "field"):
                 yield dtype, nx, ny, OPTIONS[name]
+
+
+# A batch whose calls take cascade passes: two lattices large enough to make them pay, and
+# beside them narrow, low and ragged ones, whose strips wrap several times in x or y
+POOL_SHAPES = [(1400, 1300), (1201, 1111), (3, 3), (4, 17), (5, 2003), (49, 503), (95, 78), (111, 305), (112, 170), (113, 301),
+               (114, 97), (225, 61), (226, 9), (337, 14), (6001, 3), (700, 333)]
+# steps of each call per slot: every remainder of four, below a pass, none
+POOL_COUNTS = [(8, 13, 6, 7, 3, 0, 21, 4, 5, 9, 10, 11, 12, 14, 15, 16), (5, 4, 11, 1, 10, 16, 2, 9, 8, 7, 6, 4, 3, 13, 4, 0),
+               (8, 13, 6, 7, 3, 0, 21, 4, 5, 9, 10, 11, 12, 14, 15, 16), (4,) * 16]

@@ -46,7 +46,7 @@ def run(so, code, env=None, timeout=120):
     return r.stdout
 
 
-_ROUTES = """
+PASSES = """
 import json, re
 def passes(log):
     out = []
@@ -64,6 +64,9 @@ def passes(log):
                         "xbc_kernel": "xbc", "ghost_kernel": "ghosts", "batch_step2_kernel": "pool_pair",
                         "batch_persistent2_kernel": "pool_pair"}.get(name, name))
     return out
+"""
+
+_ROUTES = PASSES + """
 res = []
 for case in json.loads(sys.stdin.read()):
     c = dict({"tile": None, "model": None, "field": False, "inlet": None}, **case)

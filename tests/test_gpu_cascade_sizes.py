@@ -1,6 +1,6 @@
 """Cascade passes at the widths where a strip's last columns, a lane's columns
 and the boundary columns fall differently, and two-step passes between the
-sizes of the other kernels: the bits of single steps (see cascade_sizes.py; the
+sizes of the other kernels, and pools: the bits of single steps (see cascade_sizes.py; the
 passes that these sizes take are checked in test_routes.py)."""
 import numpy as np
 import pytest
@@ -53,3 +53,39 @@ def test_two_step_bits_between_block_and_cascade_sizes(dtype, nx, ny, kw):
     ref = run(nx, ny, dtype, (7,), SINGLE, **kw)
     assert np.array_equal(run(nx, ny, dtype, (7,), **kw), ref)
     assert np.array_equal(run(nx, ny, dtype, (2, 5), **kw), ref)
+
+
+def alone(k, dtype, steps):
+    nx, ny = cascade_sizes.POOL_SHAPES[k]
+    with lbm.Lattice(nx, ny, 0.6 + 0.05 * k, 0.1 + 0.02 * k, dtype) as L:
+        L.set_tile(*SINGLE)
+        L.set_stream(torch.cuda.current_stream())
+        L.init_device(*pool_fields(k))
+        return L.step(steps).get_f()
+
+
+def pool_fields(k):
+    nx, ny = cascade_sizes.POOL_SHAPES[k]
+    g = torch.Generator(device="cuda").manual_seed(k)
+    r = lambda a: a * torch.randn(ny, nx, generator=g, dtype=torch.float64, device="cuda")  # noqa: E731
+    return 1.0 + r(0.01), r(0.02), r(0.02)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32", "f32s"])
+@pytest.mark.parametrize("mode", [lbm.GROUPED, lbm.GRAPH, lbm.PERSISTENT])
+def test_pool_cascade_bits(dtype, mode):
+    shapes = cascade_sizes.POOL_SHAPES
+    with lbm.Pool(sum(lbm.Pool.slot_bytes(nx, ny, dtype) for nx, ny in shapes), dtype) as P:
+        P.set_mode(mode)
+        slots = []
+        for k, (nx, ny) in enumerate(shapes):
+            slots.append(P.add(nx, ny, 0.6 + 0.05 * k, 0.1 + 0.02 * k))
+            f = pool_fields(k)
+            torch.cuda.synchronize()
+            P.init_device(slots[-1], *f)
+            P.sync()
+        for counts in cascade_sizes.POOL_COUNTS:
+            P.step(slots, np.array(counts, dtype=np.int32))
+        for k, s in enumerate(slots):
+            assert P.time(s) == sum(c[k] for c in cascade_sizes.POOL_COUNTS)
+            assert np.array_equal(P.get_f(s), alone(k, dtype, P.time(s))), (dtype, mode, shapes[k])

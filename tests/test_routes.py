@@ -69,3 +69,24 @@ def test_one_fp16_step_with_an_inlet_takes_the_faster_launches(so):
     got = fake_gpu.routes(so, [case(nx, ny, "f16s", n, **inlet)
                                for nx, ny in ((650, 650), (700, 700), (5000, 100)) for n in (1, 2)])
     assert got == [["block"], ["block"], ["step", "xbc"], ["block"], ["step", "xbc"], ["block"]]
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32", "f32s"])
+def test_the_pool_sizes_take_cascade_passes(so, dtype):
+    import cascade_sizes
+    out = fake_gpu.run(so, fake_gpu.PASSES + f"""
+for mode in (lbm.GROUPED, lbm.GRAPH, lbm.PERSISTENT):
+    P = lbm.Pool(1 << 34, {dtype!r})
+    P.set_mode(mode)
+    slots = [P.add(nx, ny, 0.7, 0.3) for nx, ny in {cascade_sizes.POOL_SHAPES!r}]
+    for s in slots: P.init_device(s, None, None, None)
+    fake.fake_log()
+    for c in {cascade_sizes.POOL_COUNTS!r}:
+        P.step(slots, np.array(c, dtype=np.int32))
+        r = passes(fake.fake_log())
+        # a replayed graph of the first call launches nothing by itself
+        assert r.count("pool_cascade4") == (1 if mode == lbm.PERSISTENT else max(c) // 4) or (mode == lbm.GRAPH and not r), (mode, c, r)
+        assert "pool_pair" in r or not any(n % 4 for n in c) or not r
+print("ok")
+""")
+    assert out.strip() == "ok"
