@@ -114,21 +114,33 @@ def cascade_steps(form, n):
     return 0 if n < 2048 else (4 if variant == "field" or dtype == "f16s" else 8)
 
 
-def launches_of(tile, steps, deep=0):
-    """Kernel launches lbm_step makes for `steps` steps in this shape: two
-    steps per launch for a two-step shape (a lone last step takes one more),
-    cascade passes of at most `deep` steps first."""
-    n = 0
-    for p in (8, 4):
-        if p <= deep:
-            n += steps // p
+def launch_kinds(tile, steps, deep=0):
+    """Kernel launches lbm_step makes for `steps` steps in this shape, by the
+    steps they take: cascade passes of at most `deep` steps first, then two
+    steps per launch for a two-step shape (a lone last step takes one more)."""
+    kinds = {}
+    for p in (8, 4, 2 if tile[3] & TWO_STEP else 1, 1):
+        if p <= max(deep, 2) and steps // p:
+            kinds[p] = steps // p
             steps %= p
-    return n + ((steps + 1) // 2 if tile[3] & TWO_STEP else steps)
+    return kinds
+
+
+def launches_of(tile, steps, deep=0):
+    """Their number."""
+    return sum(launch_kinds(tile, steps, deep).values())
+
+
+def sweep_launch_kinds(tile, steps, deep=0):
+    """The same for time_sweep's calls of CALL_STEPS steps."""
+    kinds = {p: steps // CALL_STEPS * k for p, k in launch_kinds(tile, CALL_STEPS, deep).items() if steps >= CALL_STEPS}
+    for p, k in launch_kinds(tile, steps % CALL_STEPS, deep).items():
+        kinds[p] = kinds.get(p, 0) + k
+    return kinds
 
 
 def sweep_launches(tile, steps, deep=0):
-    """The same for time_sweep's calls of CALL_STEPS steps."""
-    return steps // CALL_STEPS * launches_of(tile, CALL_STEPS, deep) + launches_of(tile, steps % CALL_STEPS, deep)
+    return sum(sweep_launch_kinds(tile, steps, deep).values())
 
 
 CALL_STEPS = 8
@@ -198,14 +210,22 @@ def measure_form(lbm, workloads, torch, n, dtype, steps, warmup, tile=None):
     tile = lats[0].get_tile()
     sec, wall = time_sweep(torch, lats, steps, warmup, stream)
     tot = [L.totals() for L in lats]
-    for L in lats:
-        L.close()
     sites = n * n * len(lats)
     # every launch reads and writes each site's nine populations once
-    launches = sweep_launches(tile, steps, deep) * len(lats)
+    kinds = sweep_launch_kinds(tile, steps, deep)
+    launches = sum(kinds.values()) * len(lats)
+    # the time of a launch of the kernel named below: where the steps took launches
+    # of several kinds, from calls of CALL_STEPS steps (which take one kind) of their own
+    kernel_us = 1e6 * sec / launches
+    if len(kinds) > 1:
+        own = 5 * CALL_STEPS
+        kernel_us = 1e6 * time_sweep(torch, lats, own, 0, stream)[0] / (sweep_launches(tile, own, deep) * len(lats))
+    for L in lats:
+        L.close()
     mlups = sites * steps / sec / 1e6
     gbs = form_bytes_per_site(dtype) * n * n / (sec / launches) / 1e9
-    return {"mlups": mlups, "ms_per_step": 1e3 * sec / steps, "kernel_us": 1e6 * sec / launches,
+    return {"mlups": mlups, "ms_per_step": 1e3 * sec / steps, "kernel_us": kernel_us,
+            "launches_by_steps": {str(p): k * len(lats) for p, k in kinds.items()},
             "achieved_GBs": gbs, "frac": gbs / PEAK_HBM_GBS, "wall_s": wall,
             "mass_total_first": tot[0][0], "kernel": kernel_name(tile, dtype, deep), "tile": list(tile)}
 
@@ -537,6 +557,7 @@ def main():
                      "traffic": measured_traffic(head["kernel"], n),
                      "kernel": head["kernel"],
                      "bytes_per_launch": BYTES_PER_SITE["f32"] * n * n,
+                     "launches_by_steps": head["launches_by_steps"],
                      "avg_launch_us": round(head["kernel_us"], 2)},
         "cpu_baseline": cpu,
         "forms": {k: {kk: (round(vv, 4) if isinstance(vv, float) else vv) for kk, vv in v.items()}

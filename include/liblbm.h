@@ -111,9 +111,9 @@ int lbm_set_model(lbm_lattice* L, int model);
  * and 1 (x = nx - 1), and the periodic seam between the two columns is
  * cut: a population that would cross it arrives as the equilibrium
  * population of the column it enters, at that column's boundary density.
- * t is lbm_time() (so lbm_init / lbm_set_f restart the inlet's phase). Each
- * step then adds one small launch (the two columns), except on lattices
- * small enough for the block kernel (see lbm_set_tile). LBM_EINVAL for a NULL
+ * t is lbm_time() (so lbm_init / lbm_set_f restart the inlet's phase). Block and
+ * cascade passes (see lbm_set_tile) apply the boundaries inside; a step that
+ * neither takes adds one small launch (the two columns). LBM_EINVAL for a NULL
  * handle, an unknown mode, or the inlet/outlet with nx < 5, a period that
  * is not finite and > 0, or |amplitude| >= 1. Takes effect at the next
  * step; pools are periodic. */

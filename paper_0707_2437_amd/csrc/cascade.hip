@@ -85,15 +85,15 @@ template <class T, bool SHIFT, int VX> struct CascadeRow {
         for (int i = 0; i < 9; ++i) k.d[i] = r[i].v[J];
         return k;
     }
-    // The results of column J (a) and, if G is 2, of the next (b), rounded
-    // to the storage type.
-    template <int J, int G>
+    // The results of column J (a) and of the next (b), rounded to the storage
+    // type.
+    template <int J>
     static __device__ __forceinline__ void store(const C (&a)[9], const C (&b)[9], Mem (&f)[9], const Centre<C>& cn)
     {
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             f[i].v[J] = from_d<T, SHIFT, C>(a[i], i, cn);
-            if constexpr (G == 2) f[i].v[J + 1] = from_d<T, SHIFT, C>(b[i], i, cn);
+            f[i].v[J + 1] = from_d<T, SHIFT, C>(b[i], i, cn);
         }
     }
 };
@@ -159,20 +159,15 @@ template <int VX> struct CascadeRow<_Float16, true, VX> {
         for (int i = 0; i < 9; ++i) k.w[i] = r[i].q[J >> 1];
         return k;
     }
-    template <int J, int G>
+    template <int J>
     static __device__ __forceinline__ void store(const float (&a)[9], const float (&b)[9], Mem (&f)[9],
                                                  const Centre<float>&)
     {
-        static_assert(G == 2, "two columns per register");
 #pragma unroll
         for (int i = 0; i < 9; ++i) f[i].q[J / 2] = pack_h2(a[i], b[i]);
     }
 };
 
-// One level's state between rows: the row it relaxes next (populations d,
-// densities w), the densities of the row above it (wp), and the planes of
-// its last results that wait for rows below: e_iy = 0 of the last row (z),
-// e_iy = 1 of the last two (up, by the row's parity).
 // A row's columns of a lane in LDS, as one aligned vector: as a struct of
 // 4-byte alignment they move in halves, with four bank conflicts each.
 template <int BYTES> struct CascadeLds {
@@ -182,6 +177,10 @@ template <int BYTES> struct CascadeLds {
 // Stands for XbcValues where the lattice is periodic in x.
 struct CascadePeriodic {};
 
+// One level's state between rows: the row it relaxes next (populations d,
+// densities w), the densities of the row above it (wp), and the planes of
+// its last results that wait for rows below: e_iy = 0 of the last row (z),
+// e_iy = 1 of the last two (up, by the row's parity).
 template <class R> struct CascadeWait {
     R z[3], up[2][3];
 };
@@ -212,8 +211,8 @@ __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t rs, const V v, 
 }
 
 // One wave's part of a tile (w: its place in the team; FIRST reads memory, LAST
-// writes it, in and outq are the LDS slots between): NS steps of rows [chunk a.h, (chunk + 1) a.h) and the strip's
-// inner columns. EDGE: a strip whose window reaches past the lattice's left
+// writes it, in and outq are the LDS slots between): NS steps of rows
+// [chunk a.h, (chunk + 1) a.h) and the strip's inner columns. EDGE: a strip whose window reaches past the lattice's left
 // or right edge; its lanes load every element from its wrapped column
 // (Sec. 4: periodic in x) and store element by element.
 template <class T, bool SHIFT, int VX, int NL, bool FIRST, bool LAST, bool FIELD, bool RC, bool EDGE, class XB>
@@ -419,7 +418,8 @@ __device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src,
             // relax the held row, its neighbour rows' densities known
             const C wl = from_left(l.w[VX - 1]), wr = from_right(l.w[0]);
             Mem f[9];
-            constexpr int G = VX < 2 ? VX : 2;  // columns at a time (registers)
+            constexpr int G = 2;  // columns at a time (registers)
+            static_assert(VX % G == 0, "pairs of columns");
             static_for<0, VX / G>([&](auto gc) {
                 constexpr int J = G * decltype(gc)::value;
                 auto relax = [&](auto jc, C (&o)[9]) {
@@ -432,8 +432,8 @@ __device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src,
                 };
                 C oa[9], ob[9];
                 relax(std::integral_constant<int, J>{}, oa);
-                if constexpr (G == 2) relax(std::integral_constant<int, J + G - 1>{}, ob);
-                R::template store<J, G>(oa, ob, f, cn);
+                relax(std::integral_constant<int, J + 1>{}, ob);
+                R::template store<J>(oa, ob, f, cn);
                 // columns, and levels, one after the other: interleaved they need more registers
                 __builtin_amdgcn_sched_barrier(0);
             });

@@ -169,6 +169,8 @@ inline unsigned* done_word(void* buf, const Geom& g, int esize)
     return (unsigned*)((char*)buf + (size_t)2 * (size_t)buffer_elems(g) * esize);
 }
 
+// Three partial sums per block of the moments, and three spare: part of what
+// lbm_footprint_bytes and lbm_pool_slot_bytes report.
 inline size_t red_doubles(const Geom& g) { return (size_t)3 * moments_blocks(g) + 3; }
 
 // The equilibrium shift of the altered-equilibrium model: 3 c^2 - 1 (its

@@ -33,7 +33,8 @@ struct Geom {
 
 // Collision / source coefficients of Eq. 5 in the delta form used by the
 // kernels (d_i = f_i - w_i; see collide_col in step.h), with om = 1/tau and
-// the index 0, 1, 2 for the rest, axis and diagonal links:
+// the index 0, 1, 2 for the rest, axis and diagonal links (rounded together,
+// see closed_coefs in host.h):
 //   om1 = 1 - om;
 //   a_k = om w_k (1 + e_k) multiplies drho in the even part, b_k (-3/2 om w_0,
 //   -3/2 om w_1, 3 om w_2) multiplies j.u, and z_k = om w_k e_k is its
