@@ -133,7 +133,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
                 buf ^= 1;
                 continue;
             }
-            StepTile a = ldc(&L->tile);
+            BatchTile a = ldc(&L->tile);
             if ((ldc(&L->t0) + s) & 1) {
                 const void* b = a.src;
                 a.src = a.dst;
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(
             }
             const int per = ldc(&L->per_item);
             const int t0 = (i - ldc(&L->item_begin)) * per;
-            const int t1 = min(t0 + per, ldc(&L->tile.nstrips) * ldc(&L->tile.nchunks));
+            const int t1 = min(t0 + per, a.nstrips * a.nchunks);
             for (int t = t0; t < t1; ++t) {
                 const bool last = t + 1 == t1;
                 const int strip = t % a.nstrips;

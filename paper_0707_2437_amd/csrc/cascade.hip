@@ -215,8 +215,8 @@ __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t rs, const V v, 
 // [chunk a.h, (chunk + 1) a.h) and the strip's inner columns. EDGE: a strip whose window reaches past the lattice's left
 // or right edge; its lanes load every element from its wrapped column
 // (Sec. 4: periodic in x) and store element by element.
-template <class T, bool SHIFT, int VX, int NL, bool FIRST, bool LAST, bool FIELD, bool RC, bool EDGE, class XB>
-__device__ __forceinline__ void cascade_tile(const StepTile& a, const void* src, void* dst, int strip, int chunk,
+template <class T, bool SHIFT, int VX, int NL, bool FIRST, bool LAST, bool FIELD, bool RC, bool EDGE, class Tile, class XB>
+__device__ __forceinline__ void cascade_tile(const Tile& a, const void* src, void* dst, int strip, int chunk,
                                              [[maybe_unused]] typename CascadeLds<sizeof(T) * VX>::type (*in)[9][64],
                                              [[maybe_unused]] typename CascadeLds<sizeof(T) * VX>::type (*outq)[9][64],
                                              int w, [[maybe_unused]] const XB& xb)
@@ -509,8 +509,8 @@ template <class T, bool SHIFT, int VX> struct CascadeRing {
 
 // One wave of a team. The waves pass the same number of barriers: a wave's
 // first row is one barrier behind that of the wave before it.
-template <class T, bool SHIFT, int VX, int NL, bool FIELD, bool RC, bool EDGE, class XB>
-__device__ __forceinline__ void cascade_wave(const StepTile& a, const void* src, void* dst, int strip, int chunk,
+template <class T, bool SHIFT, int VX, int NL, bool FIELD, bool RC, bool EDGE, class Tile, class XB>
+__device__ __forceinline__ void cascade_wave(const Tile& a, const void* src, void* dst, int strip, int chunk,
                                              CascadeRing<T, SHIFT, VX>& ring, const XB& xb)
 {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -563,13 +563,14 @@ __global__ __launch_bounds__(64 * kCascadeWaves) __attribute__((amdgpu_waves_per
     const bool odd = ((L.t0 + p) & 1) != 0;
     const void* src = odd ? L.tile.dst : L.tile.src;
     void* dst = odd ? const_cast<void*>(L.tile.src) : L.tile.dst;
+    const BatchTile& a = L.tile;
     const int t = i - L.item_begin;
-    const int strip = t % L.tile.nstrips, chunk = t / L.tile.nstrips;
+    const int strip = t % a.nstrips, chunk = t / a.nstrips;
     const int x0 = strip * W - HL * VX;
-    if (x0 - 1 < 0 || x0 + 64 * VX + 1 > L.tile.g.nx)
-        cascade_wave<T, SHIFT, VX, NL, false, RC, true>(L.tile, src, dst, strip, chunk, ring, CascadePeriodic{});
+    if (x0 - 1 < 0 || x0 + 64 * VX + 1 > a.g.nx)
+        cascade_wave<T, SHIFT, VX, NL, false, RC, true>(a, src, dst, strip, chunk, ring, CascadePeriodic{});
     else
-        cascade_wave<T, SHIFT, VX, NL, false, RC, false>(L.tile, src, dst, strip, chunk, ring, CascadePeriodic{});
+        cascade_wave<T, SHIFT, VX, NL, false, RC, false>(a, src, dst, strip, chunk, ring, CascadePeriodic{});
 }
 
 // Persistent form: all npasses passes of a batch in one launch, members and
@@ -605,7 +606,7 @@ batch_persistent_cascade_kernel(const BatchLat* __restrict__ lats, const int* __
             if (i >= nitems) break;
             const BatchLat* L = &lats[ldc(&item_lat[i])];
             if (p >= ldc(&L->nsteps)) continue;  // this lattice takes fewer passes
-            const StepTile a = ldc(&L->tile);
+            const BatchTile a = ldc(&L->tile);
             const bool odd = ((ldc(&L->t0) + p) & 1) != 0;
             const void* src = odd ? a.dst : a.src;
             void* dst = odd ? const_cast<void*>(a.src) : a.dst;

@@ -221,14 +221,11 @@ template <class C> inline CoefSet<C> closed_coefs(double tau, double c2, int mod
     k.b1 = -(k.t45 + k.b0 / 2);  // a difference of numbers within a factor of two: exact
     k.b2 = -k.b1 / 2;
     k.as1 = (C)(model == LBM_MODEL_EQUILIBRIUM ? 0.0 : source_as1(c2));
-    if constexpr (sizeof(C) == sizeof(double)) {
-        k.z0 = (C)(om * 4 / 9 * e0);
-        k.z1 = -k.z0 / 5;
-        k.z2 = -k.z0 / 4 - k.z1;  // exact, as b1
-    } else {
-        k.e1 = (C)e1;
-        k.e0 = (C)e0;
-    }
+    k.z0 = (C)(om * 4 / 9 * e0);
+    k.z1 = -k.z0 / 5;
+    k.z2 = -k.z0 / 4 - k.z1;  // exact, as b1
+    k.e1 = (C)e1;
+    k.e0 = (C)e0;
     return k;
 }
 
@@ -237,12 +234,9 @@ template <class C> inline CoefSet<C> closed_coefs(double tau, double c2, int mod
 // no source term and shifts the equilibrium instead: for i != 0, feq_i - w_i
 // gains w_i rho (3 c^2 - 1); feq_0 loses the sum of those,
 // (5/9) rho (3 c^2 - 1) = w_0 rho (5/4)(3 c^2 - 1).
-inline Coef make_coef(int dtype, double tau, double c2, int model)
+inline Coef make_coef(double tau, double c2, int model)
 {
-    Coef k;
-    if (dtype == LBM_F64) k.d = closed_coefs<double>(tau, c2, model);
-    else k.f = closed_coefs<float>(tau, c2, model);
-    return k;
+    return Coef{closed_coefs<double>(tau, c2, model), closed_coefs<float>(tau, c2, model)};
 }
 
 // A c2 field: row pitch (elements) and bytes of the per-site coefficient

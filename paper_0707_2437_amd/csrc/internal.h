@@ -46,20 +46,11 @@ struct Geom {
 //   power-of-two scaling).
 // e1, e0 shift the equilibrium for the altered-equilibrium model (0 for the
 // paper's model): e1 for the moving links (e_1 = e_2), e0 for the rest one.
-// FP32 arithmetic, centred on the state at rest, has them in its centre and no
-// z_k.
-template <class C> struct CoefTerms {
-    C om1, a0, a1, a2, b0, b1, b2, t45, t9, w3, as1;
+template <class C> struct CoefSet {
+    C om1, a0, a1, a2, b0, b1, b2, z0, z1, z2, t45, t9, w3, as1, e1, e0;
 };
-template <class C> struct CoefSet;
-template <> struct CoefSet<double> : CoefTerms<double> {
-    double z0, z1, z2;
-};
-template <> struct CoefSet<float> : CoefTerms<float> {
-    float e1, e0;
-};
-// In the lattice's compute precision.
-union Coef {
+// In FP64 and in FP32, each closed by itself.
+struct Coef {
     CoefSet<double> d;
     CoefSet<float> f;
 };
@@ -78,8 +69,8 @@ struct StepTile {
     // Per-site source coefficients (a c2 field): field[y * fpitch + x] =
     // as1 at site (x, y) in compute precision; nullptr for the uniform one
     // of c.
-    int fpitch;
     const void* field;
+    int fpitch;
 };
 
 // A dispatch's work-item count is 32-bit: launchers refuse a grid that
@@ -103,15 +94,31 @@ __host__ __device__ inline double source_as1(double c2)
 // The batch's work is cut into items of up to `per_item` consecutive tiles
 // of one lattice; item i belongs to lattice item_lat[i] (a device array),
 // and the lattice's items are item_begin .. item_begin + nitems - 1.
-// Its size counts: arrays of descriptors of up to 16 KiB (78 lattices) reach the
-// device in 3 us, larger ones in 15 more.
+// Its size counts: arrays of descriptors of up to 16 KiB (97 lattices) reach the
+// device in 3 us, larger ones in 15 more. So it holds what the batched kernels
+// read: pools step the paper's model (e = z = 0), without c2 fields, and the
+// coefficients are those of the pool's compute precision.
+template <class C> struct BatchCoefSet {
+    C om1, a0, a1, a2, b0, b1, b2, t45, t9, w3, as1;
+};
+union BatchCoef {
+    BatchCoefSet<double> d;
+    BatchCoefSet<float> f;
+};
+struct BatchTile {  // members as in StepTile
+    const void* src;
+    void* dst;
+    Geom g;
+    BatchCoef c;
+    int h, nstrips, nchunks;
+};
 struct BatchLat {
-    StepTile tile;   // of tile.nstrips * tile.nchunks tiles
+    BatchTile tile;  // of tile.nstrips * tile.nchunks tiles
     int t0;          // parity of the lattice's time when the call starts
     int nsteps;      // steps this lattice takes in the call
     int item_begin;  // first batch item of this lattice
     int per_item;    // tiles per item
 };
-static_assert(sizeof(BatchLat) <= 208, "78 descriptors in 16 KiB");
+static_assert(sizeof(BatchLat) <= 168, "97 descriptors in 16 KiB");
 
 }  // namespace lbm

@@ -205,18 +205,19 @@ size_t slot_bytes(int nx, int ny, int dtype, Geom* g_out, size_t* red_at = nullp
 // The descriptor of a slot for vertical-stack tiles of vx columns per lane
 // and nw waves (the shape of the launch that reads it); two: the two-step
 // tiles of step2_cols / step2_rows.
-StepTile slot_tile(const Slot& S, int vx, int nw, int two)
+BatchTile slot_tile(const Slot& S, int dtype, int vx, int nw, int two)
 {
-    StepTile t{};
+    BatchTile t{};
     t.src = S.b0;
     t.dst = S.b1;
     t.g = S.g;
-    t.c = S.coef;
+    auto set = [](auto& b, const auto& k) { b = {k.om1, k.a0, k.a1, k.a2, k.b0, k.b1, k.b2, k.t45, k.t9, k.w3, k.as1}; };
+    if (dtype == LBM_F64) set(t.c.d, S.coef.d);
+    else set(t.c.f, S.coef.f);
     t.h = nw - 2;
     const int W = two ? step2_cols(vx) : 64 * vx, R = two ? step2_rows(nw) : nw - 2;
     t.nstrips = (S.nx + W - 1) / W;
     t.nchunks = (S.ny + R - 1) / R;
-    t.rowband = 1;
     return t;
 }
 
@@ -373,7 +374,7 @@ CascadeShape pool_cascade(lbm_pool* P, const int* slots, const int* nsteps, int 
 void add_cascade(lbm_pool* P, const Slot& S, const CascadeShape& c, int passes, long long buffer_t0)
 {
     BatchLat b{};
-    b.tile = slot_tile(S, P->vx, P->nw, P->two);
+    b.tile = slot_tile(S, P->dtype, P->vx, P->nw, P->two);
     const int w = cascade_cols(cascade_vx(P->dtype), kCascadeWaves, P->esize);
     // chunks of even height, a whole number of the kernel's turns of four rows
     const int chunks = (S.ny + c.h - 1) / c.h;
@@ -482,7 +483,7 @@ int lbm_pool_add(lbm_pool* P, int nx, int ny, double tau, double c2)
     S.tau = tau;
     S.c2 = c2;
     S.g = g;
-    S.coef = make_coef(P->dtype, tau, c2, LBM_MODEL_FORCING);
+    S.coef = make_coef(tau, c2, LBM_MODEL_FORCING);
     S.bytes = bytes;
     const size_t fb = footprint(g, P->esize);
     S.span = bytes;
@@ -580,7 +581,7 @@ static int build_batch(lbm_pool* P, const int* slots, const int* nsteps, int cou
         if (n == 0) continue;
         const Slot& S = P->slots[slots[k]];
         BatchLat b{};
-        b.tile = slot_tile(S, P->vx, P->nw, P->two);
+        b.tile = slot_tile(S, P->dtype, P->vx, P->nw, P->two);
         b.t0 = (int)(buffer_time(S) & 1);
         b.nsteps = n;
         add_lattice(P, b);
@@ -871,7 +872,7 @@ int lbm_pool_autotune(lbm_pool* P, const int* slots, int count, int reps, int us
                 continue;
             }
             BatchLat b{};
-            b.tile = slot_tile(P->slots[slots[j]], k.vx, k.nw, two);
+            b.tile = slot_tile(P->slots[slots[j]], P->dtype, k.vx, k.nw, two);
             b.t0 = (int)(buffer_time(P->slots[slots[j]]) & 1);
             b.nsteps = two ? 2 : 1;
             add_lattice(P, b);

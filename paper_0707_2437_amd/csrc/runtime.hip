@@ -286,7 +286,7 @@ lbm_lattice* lbm_create(int nx, int ny, double tau, double c2, int dtype)
     L->c2 = c2;
     L->g = make_geom(nx, ny, L->esize, choose_interleaved(nx, ny, dtype));
     L->model = LBM_MODEL_FORCING;
-    L->coef = make_coef(dtype, tau, c2, L->model);
+    L->coef = make_coef(tau, c2, L->model);
     const TileDefault td = default_tile(dtype);
     L->vx = td.vx;
     L->nw = td.nw;
@@ -448,7 +448,7 @@ int lbm_set_model(lbm_lattice* L, int model)
         if (e != hipSuccess) return status_of(e);
     }
     L->model = model;
-    L->coef = make_coef(L->dtype, L->tau, L->c2, model);
+    L->coef = make_coef(L->tau, L->c2, model);
     return LBM_OK;
 }
 

@@ -376,13 +376,22 @@ template <class C> __device__ __forceinline__ CoefC<C> coef_c(const Coef& k)
     else return k.d;
 }
 
+// A batch's lattice (e = z = 0).
+template <class C> __device__ __forceinline__ CoefC<C> coef_c(const BatchCoef& k)
+{
+    const BatchCoefSet<C>* c;
+    if constexpr (sizeof(C) == sizeof(float)) c = &k.f;
+    else c = &k.d;
+    return CoefC<C>{c->om1, c->a0, c->a1, c->a2, c->b0, c->b1, c->b2, C(0), C(0), C(0), c->t45, c->t9, c->w3, c->as1, C(0), C(0)};
+}
+
 // The centre in compute precision (see Centre): w_i (1 + e) for FP32, which
 // is w_i itself for the paper's model (e = 0); w_i for FP64.
 // Only the model's shifts are read, so the centre is all a tile holds of
 // the coefficients while its loads are in flight.
-template <class C, bool RC = ModelCentred<C>::value> __device__ __forceinline__ Centre<C> centre_c(const Coef& c)
+template <class C, bool RC = ModelCentred<C>::value, class K> __device__ __forceinline__ Centre<C> centre_c(const K& c)
 {
-    if constexpr (RC) {
+    if constexpr (RC && !std::is_same<K, BatchCoef>::value) {
         const CoefC<C> k = coef_c<C>(c);
         return Centre<C>{wt<C>(0) * (C(1) + k.e0), wt<C>(1) * (C(1) + k.e1), wt<C>(5) * (C(1) + k.e1)};
     } else {
@@ -421,18 +430,13 @@ __device__ __forceinline__ void collide_col(const V& v, C drho, C gx, C gy, cons
     const C ux = jx * ir, uy = jy * ir;
     const C tx = jx * ux, ty = jy * uy, txy = jx * uy;
     const C s = tx + ty;
-    C p0, pa, pd;
-    if constexpr (RC || sizeof(C) == sizeof(float)) {
-        p0 = fmac(k.a0, drho, k.b0 * s);
-        pa = fmac(k.a1, drho, k.b1 * s);
-        pd = fmac(k.a2, drho, k.b2 * s);
-    } else {
-        p0 = fmac(k.a0, drho, fmac(k.b0, s, k.z0));
-        pa = fmac(k.a1, drho, fmac(k.b1, s, k.z1));
-        pd = fmac(k.a2, drho, fmac(k.b2, s, k.z2));
-    }
+    auto even = [&](C a, C b, C z) {
+        if constexpr (RC || sizeof(C) == sizeof(float)) return fmac(a, drho, b * s);
+        else return fmac(a, drho, fmac(b, s, z));
+    };
+    const C pa = even(k.a1, k.b1, k.z1), pd = even(k.a2, k.b2, k.z2);
     const C q1 = fmac(k.as1, gx, k.w3 * jx), q2 = fmac(k.as1, gy, k.w3 * jy);
-    o[0] = v.fma(k.om1, 0, p0);
+    o[0] = v.fma(k.om1, 0, even(k.a0, k.b0, k.z0));
     const C p1 = fmac(k.t45, tx, pa), p2 = fmac(k.t45, ty, pa);
     o[1] = v.fma(k.om1, 1, p1 + q1);
     o[3] = v.fma(k.om1, 3, p1 - q1);
@@ -699,7 +703,7 @@ template <class T, bool SHIFT, int VX, int NW, bool NTS, bool FIELD, bool RC> st
     C w[WV];             // densities of the window columns
 
     // issue_rows / land_rows: the phases for a lane with r.load set.
-    template <bool EDGE> __device__ __forceinline__ void issue_rows(const StepTile& a, const void* src, const VRow& r)
+    template <bool EDGE, class Tile> __device__ __forceinline__ void issue_rows(const Tile& a, const void* src, const VRow& r)
     {
         const char* sb[9];
         src_bases<T>(src, a.g, sb);
@@ -710,7 +714,7 @@ template <class T, bool SHIFT, int VX, int NW, bool NTS, bool FIELD, bool RC> st
 
     // The loads consumed: populations of the own columns (d) and densities
     // of the window columns (w).
-    __device__ __forceinline__ void land_regs(const StepTile& a)
+    template <class Tile> __device__ __forceinline__ void land_regs(const Tile& a)
     {
         const Centre<C> cn = centre_c<C, RC>(a.c);
         K tmp[9][WV];
@@ -726,19 +730,19 @@ template <class T, bool SHIFT, int VX, int NW, bool NTS, bool FIELD, bool RC> st
             for (int j = 0; j < VX; ++j) d[i][j] = tmp[i][j + 1];
     }
 
-    __device__ __forceinline__ void land_rows(const StepTile& a, const VRow& r, Lds& lds)
+    template <class Tile> __device__ __forceinline__ void land_rows(const Tile& a, const VRow& r, Lds& lds)
     {
         land_regs(a);
 #pragma unroll
         for (int j = 0; j < VX; ++j) lds[r.wave][r.lane * VX + j] = w[j + 1];
     }
 
-    template <bool EDGE> __device__ __forceinline__ void issue(const StepTile& a, const void* src, const VRow& r)
+    template <bool EDGE, class Tile> __device__ __forceinline__ void issue(const Tile& a, const void* src, const VRow& r)
     {
         if (r.load) issue_rows<EDGE>(a, src, r);
     }
     // issue with the edge patch chosen at run time (see gather_raw_rt)
-    __device__ __forceinline__ void issue_rt(const StepTile& a, const void* src, const VRow& r, bool edge)
+    template <class Tile> __device__ __forceinline__ void issue_rt(const Tile& a, const void* src, const VRow& r, bool edge)
     {
         if (r.load) {
             const char* sb[9];
@@ -748,19 +752,19 @@ template <class T, bool SHIFT, int VX, int NW, bool NTS, bool FIELD, bool RC> st
                 if (r.relax) af = field_row<C, VX>(a, r.y, r.x);
         }
     }
-    __device__ __forceinline__ void land(const StepTile& a, const VRow& r, Lds& lds)
+    template <class Tile> __device__ __forceinline__ void land(const Tile& a, const VRow& r, Lds& lds)
     {
         if (r.load) land_rows(a, r, lds);
     }
 
-    __device__ __forceinline__ void relax(const StepTile& a, void* dst, const VRow& r, const Lds& lds)
+    template <class Tile> __device__ __forceinline__ void relax(const Tile& a, void* dst, const VRow& r, const Lds& lds)
     {
         relax_g(a, dst, r, [&](int j) { return lds[r.wave + 1][r.lane * VX + j] - lds[r.wave - 1][r.lane * VX + j]; });
     }
 
     // relax with gy(j) the undivided y difference rho(y + 1) - rho(y - 1) at
     // the lane's column j
-    template <class GY> __device__ __forceinline__ void relax_g(const StepTile& a, void* dst, const VRow& r, GY&& gyf)
+    template <class Tile, class GY> __device__ __forceinline__ void relax_g(const Tile& a, void* dst, const VRow& r, GY&& gyf)
     {
         if (r.relax) {
             char* dbase[9];
@@ -799,7 +803,7 @@ template <class T, bool SHIFT, int VX, int NW, bool NTS, bool FIELD, bool RC> st
     unsigned u[9][NWD];
     float w[WV];
 
-    template <bool EDGE> __device__ __forceinline__ void issue_rows(const StepTile& a, const void* src, const VRow& r)
+    template <bool EDGE, class Tile> __device__ __forceinline__ void issue_rows(const Tile& a, const void* src, const VRow& r)
     {
         static_assert(!EDGE, "ghost columns make the patch unnecessary");
         // An odd-length window (VX = 1) loads one half past its end (at most
@@ -811,7 +815,7 @@ template <class T, bool SHIFT, int VX, int NW, bool NTS, bool FIELD, bool RC> st
             if (r.relax) af = field_row<float, VX>(a, r.y, r.x);
     }
 
-    __device__ __forceinline__ void land_regs(const StepTile&)
+    template <class Tile> __device__ __forceinline__ void land_regs(const Tile&)
     {
 #pragma unroll
         for (int i = 0; i < 9; ++i)
@@ -823,32 +827,32 @@ template <class T, bool SHIFT, int VX, int NW, bool NTS, bool FIELD, bool RC> st
         });
     }
 
-    __device__ __forceinline__ void land_rows(const StepTile& a, const VRow& r, Lds& lds)
+    template <class Tile> __device__ __forceinline__ void land_rows(const Tile& a, const VRow& r, Lds& lds)
     {
         land_regs(a);
 #pragma unroll
         for (int j = 0; j < VX; ++j) lds[r.wave][r.lane * VX + j] = w[j + 1];
     }
 
-    template <bool EDGE> __device__ __forceinline__ void issue(const StepTile& a, const void* src, const VRow& r)
+    template <bool EDGE, class Tile> __device__ __forceinline__ void issue(const Tile& a, const void* src, const VRow& r)
     {
         if (r.load) issue_rows<EDGE>(a, src, r);
     }
-    __device__ __forceinline__ void issue_rt(const StepTile& a, const void* src, const VRow& r, bool)
+    template <class Tile> __device__ __forceinline__ void issue_rt(const Tile& a, const void* src, const VRow& r, bool)
     {
         if (r.load) issue_rows<false>(a, src, r);
     }
-    __device__ __forceinline__ void land(const StepTile& a, const VRow& r, Lds& lds)
+    template <class Tile> __device__ __forceinline__ void land(const Tile& a, const VRow& r, Lds& lds)
     {
         if (r.load) land_rows(a, r, lds);
     }
 
-    __device__ __forceinline__ void relax(const StepTile& a, void* dst, const VRow& r, const Lds& lds)
+    template <class Tile> __device__ __forceinline__ void relax(const Tile& a, void* dst, const VRow& r, const Lds& lds)
     {
         relax_g(a, dst, r, [&](int j) { return lds[r.wave + 1][r.lane * VX + j] - lds[r.wave - 1][r.lane * VX + j]; });
     }
 
-    template <class GY> __device__ __forceinline__ void relax_g(const StepTile& a, void* dst, const VRow& r, GY&& gyf)
+    template <class Tile, class GY> __device__ __forceinline__ void relax_g(const Tile& a, void* dst, const VRow& r, GY&& gyf)
     {
         if (r.relax) {
             char* dbase[9];
@@ -891,8 +895,8 @@ using VTile = typename std::conditional<std::is_same<T, _Float16>::value, VTileH
 // code; the others issue their loads and start the arithmetic as the loads
 // land, with no patch code in between.
 template <class T, bool SHIFT, int VX, int NW, bool NTS, bool FIELD = false,
-          bool RC = ModelCentred<typename CompT<T>::type>::value>
-__device__ __forceinline__ void vstack_tile(const StepTile& a, const void* src, void* dst, int strip, int grp,
+          bool RC = ModelCentred<typename CompT<T>::type>::value, class Tile>
+__device__ __forceinline__ void vstack_tile(const Tile& a, const void* src, void* dst, int strip, int grp,
                                             typename CompT<T>::type (&lds)[NW][64 * VX])
 {
     using V = VTile<T, SHIFT, VX, NW, NTS, FIELD, RC>;

@@ -136,7 +136,7 @@ template <class T, int VX, int NW> struct Step2Lds {
 // sharing one instantiation between the grouped and persistent batched
 // kernels made the compiler spill registers in the grouped one).
 template <class T, bool SHIFT, int VX, int NW, bool NTS, bool FIELD, bool RC, int KIND = 0>
-__device__ __forceinline__ void step2_tile(const StepTile& a, const void* src, void* dst, int strip, int grp,
+__device__ __forceinline__ void step2_tile(const BatchTile& a, const void* src, void* dst, int strip, int grp,
                                            bool single, Step2Lds<T, VX, NW>& lds)
 {
     using C = typename CompT<T>::type;
@@ -548,13 +548,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1
             const int n = ldc(&L->nsteps);
             if (2 * p >= n) continue;  // this lattice takes fewer steps
             const bool single = 2 * p + 1 == n;
-            const StepTile a = ldc(&L->tile);
+            const BatchTile a = ldc(&L->tile);
             const bool odd = ((ldc(&L->t0) + p) & 1) != 0;
             const void* src = odd ? a.dst : a.src;
             void* dst = odd ? const_cast<void*>(a.src) : a.dst;
             const int per = ldc(&L->per_item);
             const int t0 = (i - ldc(&L->item_begin)) * per;
-            const int t1 = min(t0 + per, ldc(&L->tile.nstrips) * ldc(&L->tile.nchunks));
+            const int t1 = min(t0 + per, a.nstrips * a.nchunks);
             for (int t = t0; t < t1; ++t) {
                 if (t > t0) __syncthreads();  // lds of the previous tile is still being read
                 step2_tile<T, SHIFT, VX, NW, NTS, false, false, 1>(a, src, dst, t % a.nstrips, t / a.nstrips,
